@@ -79,6 +79,34 @@ bool few_rows_ok(const cci::ProductArgs& a) {
   return cci::spmm_bits_supports(a.N, a.C, a.O, a.G, a.K);
 }
 
+// AUTO's last word on a bf16 product that the shape rules of cci_auto_algo
+// leave to the narrow, dense-tile, tap-chunk or sparse-MAC kernels: the
+// split-reduction kernels take the ones of few tiles, and they and the
+// tap-chunk kernels also run reductions in blocks of 8 (one tap) and a
+// ragged last output tile.
+cci_algo ragged_route(const cci::ProductArgs& a, cci_algo chosen) {
+  if (chosen != CCI_ALGO_NARROW_MFMA && chosen != CCI_ALGO_DENSE_TILE_MFMA && chosen != CCI_ALGO_SPARSE_MAC &&
+      chosen != CCI_ALGO_TAP_TILE_MFMA)
+    return chosen;
+  // Few 64 x 32 tiles: the split-reduction kernels (us, split / best other:
+  // 49 x 1344 -> 224 7.0 / 14.0; 196 x 816 -> 136 5.2 / 11.1; 196 x 136 ->
+  // 816 4.8 / 6.8; 784 x 512 -> 128 5.2 / 8.0; 392 x 2048 -> 512 11.2 / 18.4;
+  // 300 x 1184 -> 624 10.1 / 13.6).  From half a round of the chip on, longer
+  // reductions go to the tap-chunk kernels (3136 x 1344 -> 224 17.5 / 15.4;
+  // 700 x 1184 -> 624 15.7 / 13.6).
+  const int64_t t64x32 = (a.N + 63) / 64 * ((a.O + 31) / 32);
+  if (a.C >= 64 && t64x32 <= (a.C <= 1024 ? 256 : 128) && cci::split_k_takes(a)) return CCI_ALGO_SPLIT_K_MFMA;
+  // From 96 columns on the tap-chunk kernels are ahead of the dense-tile ones
+  // (us, tap / dense or narrow: 12544 x 576 -> 96 10.6 / 14.7; 12544 x 96 ->
+  // 576 11.1 / 17.1; 6272 x 192 -> 1152 12.2 / 21.2; 12544 x 816 -> 136 15.6
+  // / 1054 on the sparse-MAC kernels; a 3x3 stride-2 convolution 64 -> 64 over
+  // 200 704 output pixels 52.8 / 80.7), except where the narrow ones stream
+  // >= 100 K rows (200704 x 192 -> 32 28.6 / 24.0).
+  if (a.C >= 96 && !(chosen == CCI_ALGO_NARROW_MFMA && a.N >= 100000) && cci::tap_tile_takes(a))
+    return CCI_ALGO_TAP_TILE_MFMA;
+  return chosen;
+}
+
 cci_status run_product(cci::ProductArgs& a, cci_algo algo, const cci_epilogue* ep,
                        void* stream) {
   a.scale = ep ? ep->scale : nullptr;
@@ -119,6 +147,9 @@ cci_status run_product(cci::ProductArgs& a, cci_algo algo, const cci_epilogue* e
     chosen = cci::tap_tile_supports(a) ? CCI_ALGO_TAP_TILE_MFMA : tile_ok ? CCI_ALGO_DENSE_TILE_MFMA : CCI_ALGO_SPARSE_MAC;
   if (algo == CCI_ALGO_AUTO && chosen == CCI_ALGO_SPLIT_K_MFMA && !cci::split_k_supports(a))
     chosen = tile_ok ? CCI_ALGO_DENSE_TILE_MFMA : CCI_ALGO_SPARSE_MAC;
+  if (algo == CCI_ALGO_AUTO) chosen = ragged_route(a, chosen);
+  // (a pinned family takes its whole tiles only; AUTO also its ragged forms)
+  const bool pinned = algo != CCI_ALGO_AUTO;
   if (chosen == CCI_ALGO_SPARSE_MAC && !mac_ok)
     return fail(CCI_EUNSUPPORTED, "sparse-MAC kernels need G in {2,4,8,16,32} (G=%d)", a.G);
   if (chosen == CCI_ALGO_DENSE_TILE_MFMA && !tile_ok)
@@ -141,7 +172,7 @@ cci_status run_product(cci::ProductArgs& a, cci_algo algo, const cci_epilogue* e
                 "narrow MFMA kernels need bf16 X/vals, C <= 256, C %% 8 == 0, O %% 4 == 0, G <= 256, "
                 "aligned pointers, and for a conv other than 1x1 stride 1 unpadded Cin %% 8 == 0 or "
                 "Cin == 4 with an even KW");
-  if (chosen == CCI_ALGO_TAP_TILE_MFMA && !cci::tap_tile_supports(a))
+  if (chosen == CCI_ALGO_TAP_TILE_MFMA && pinned && !cci::tap_tile_supports(a))
     return fail(CCI_EUNSUPPORTED,
                 "tap-tile MFMA kernels need bf16 X/vals, Cin (FC: C) %% 64 == 0, O %% 128 == 0 with 32 %% G == 0 "
                 "or O %% 64 == 0 with 16 %% G == 0, 2 K <= G or K == G, at most 32 filter taps and aligned "
@@ -150,7 +181,7 @@ cci_status run_product(cci::ProductArgs& a, cci_algo algo, const cci_epilogue* e
     return fail(CCI_EUNSUPPORTED,
                 "stream-tile MFMA kernels need bf16 X/vals, an FC or stride-1 unpadded 1x1 product, "
                 "C %% 64 == 0 with C <= 256, O %% 64 == 0, 32 %% G == 0 and aligned pointers");
-  if (chosen == CCI_ALGO_SPLIT_K_MFMA && !cci::split_k_supports(a))
+  if (chosen == CCI_ALGO_SPLIT_K_MFMA && pinned && !cci::split_k_supports(a))
     return fail(CCI_EUNSUPPORTED,
                 "split-K MFMA kernels need bf16 X/vals, an FC or stride-1 unpadded 1x1 product, "
                 "C %% 32 == 0, O %% 16 == 0, K <= 4 and 16-byte aligned pointers");
@@ -337,8 +368,16 @@ cci_algo cci_auto_algo(cci_dtype x_t, cci_dtype val_t, int64_t N, int64_t C, int
   // 256 x 256 tiles (>= 128 of them) run on the wide-tile kernels: 2.2-2.4x
   // the dense-tile kernel on 4096^3, and level with the tap-chunk kernels on
   // ResNet-50's 1x1 layers with 196 such tiles.
+  // They run one such tile per CU, so a last round of the chip that is mostly
+  // empty costs a whole one: below 72% full rounds the tap-chunk kernels are
+  // ahead (us, wide / tap: 4096 x 4096 -> 4096, 256 tiles, 95 / 157; 4096 x
+  // 4096 -> 3072, 192 tiles, 95 / 121; 12544 x 256 -> 1024, 196 tiles, 21 /
+  // 23; 4096 x 2048 -> 2048, 128 tiles, 58 / 47; 8192 x 4096 -> 1024, 128
+  // tiles, 101 / 82).
   const int64_t tiles256 = (N + 255) / 256 * (O / 256);
-  if (bf && C == cin && C % 64 == 0 && C >= 256 && O % 256 == 0 && tiles256 >= 128) return CCI_ALGO_WIDE_TILE_MFMA;
+  const bool wide_full = 100 * tiles256 >= 72 * 256 * ((tiles256 + 255) / 256);
+  if (bf && C == cin && C % 64 == 0 && C >= 256 && O % 256 == 0 && tiles256 >= 128 && (wide_full || !tap_shape))
+    return CCI_ALGO_WIDE_TILE_MFMA;
   if (tap_shape) return CCI_ALGO_TAP_TILE_MFMA;
   const bool tile_shape = bf && cin % 32 == 0;
   if (tile_shape && (32 * static_cast<int64_t>(K) > G || !mac_g)) return CCI_ALGO_DENSE_TILE_MFMA;

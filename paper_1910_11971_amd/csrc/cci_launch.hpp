@@ -92,7 +92,10 @@ hipError_t launch_resident(const ProductArgs& a, hipStream_t s);
 // reduction splits into chunks of 64 channels under one tap (Cin % 64 == 0):
 // 128 x 128 workgroup tiles, two workgroups per CU (bf16; O % 128 == 0,
 // 32 % G == 0, KH * KW <= 32).
+// tap_tile_takes: also O % 8 == 0 (a ragged last output tile) and, for one
+// tap, C % 8 == 0 (a short last chunk); AUTO uses these.
 bool tap_tile_supports(const ProductArgs& a);
+bool tap_tile_takes(const ProductArgs& a);
 hipError_t launch_tap_tile(const ProductArgs& a, hipStream_t s);
 
 // FC products and stride-1 1x1 convolutions with 64 <= C <= 256: a workgroup
@@ -106,7 +109,9 @@ hipError_t launch_stream_tile(const ProductArgs& a, hipStream_t s);
 // reduction of one 16 RF x 16 OF tile, each building its weight fragments in
 // registers from the packed entries (bf16 X/vals; FC or stride-1 unpadded
 // 1x1; C % 32 == 0, O % 16 == 0, K <= 4).
+// split_k_takes: also C % 8 == 0 and O % 8 == 0; AUTO uses these.
 bool split_k_supports(const ProductArgs& a);
+bool split_k_takes(const ProductArgs& a);
 hipError_t launch_split_k(const ProductArgs& a, hipStream_t s);
 
 // Balanced sparsity (groups of G inputs in one output row) and the 2:4

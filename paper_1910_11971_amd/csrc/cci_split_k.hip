@@ -52,7 +52,7 @@ struct KParams {
   const void* residual;
   void* Y;
   int32_t N, C, O, G, relu;
-  int32_t nob;    // output blocks (O / (16 OF))
+  int32_t nob;    // output blocks (O / (16 OF), rounded up)
   int32_t tiles;  // row blocks x output blocks
   int32_t tpx;    // tiles per XCD (ceil(tiles / 8))
 };
@@ -125,7 +125,9 @@ __global__ __launch_bounds__(kThreads) void split_k_kernel(KParams p) {
   uint32_t rrx[OF];
 #pragma unroll
   for (int f = 0; f < OF; ++f) {
-    const int32_t o = o0 + 16 * f + lr;
+    // (a lane past O, in a ragged last block, reads the last output's group:
+    // its sums are never stored)
+    const int32_t o = min(o0 + 16 * f + lr, p.O - 1);
     const int32_t g = o / p.G;
     rrx[f] = static_cast<uint32_t>(o - g * p.G) * 0x01010101u;
     gbase[f] = static_cast<int64_t>(WL ? g - g_lo : g) * K * p.C;
@@ -135,7 +137,7 @@ __global__ __launch_bounds__(kThreads) void split_k_kernel(KParams p) {
 #pragma unroll
   for (int r = 0; r < RF; ++r) {
     const int32_t n = min(n0 + 16 * r + lr, p.N - 1);
-    xrow[r] = p.X + static_cast<int64_t>(n) * p.C + 8 * lq;
+    xrow[r] = p.X + static_cast<int64_t>(n) * p.C;
   }
 
   f32x4_t acc[RF][OF];
@@ -144,7 +146,12 @@ __global__ __launch_bounds__(kThreads) void split_k_kernel(KParams p) {
 #pragma unroll
     for (int f = 0; f < OF; ++f) acc[r][f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  const int32_t nks = p.C / 32;
+  const int32_t nks = (p.C + 31) / 32;
+  // C % 32 != 0: in the last k-step the lanes whose 8 columns lie past C read
+  // the row's first columns instead and put zeros into both operands
+  const int32_t s_rag = p.C % 32 != 0 ? nks - 1 : -1;
+  const bool lane_in = s_rag < 0 || 32 * s_rag + 8 * lq < p.C;
+  const auto lane_c0 = [&](int32_t s) { return s == s_rag && !lane_in ? 0 : 32 * s + 8 * lq; };
   Step<RF, OF, K> st[U];
   const auto load_batch = [&](int32_t s0) {
 #pragma unroll
@@ -152,9 +159,9 @@ __global__ __launch_bounds__(kThreads) void split_k_kernel(KParams p) {
       const int32_t s = s0 + kWaves * j;
       if (s < nks) {
 #pragma unroll
-        for (int r = 0; r < RF; ++r) st[j].x[r] = *reinterpret_cast<const u32x4_t*>(xrow[r] + 32 * s);
+        for (int r = 0; r < RF; ++r) st[j].x[r] = *reinterpret_cast<const u32x4_t*>(xrow[r] + lane_c0(s));
         if (!WL) {
-          const int32_t c0 = 32 * s + 8 * lq;
+          const int32_t c0 = lane_c0(s);
 #pragma unroll
           for (int f = 0; f < OF; ++f)
 #pragma unroll
@@ -173,9 +180,9 @@ __global__ __launch_bounds__(kThreads) void split_k_kernel(KParams p) {
   // the reduction (the barriers below publish them)
   {
     const int32_t tid = static_cast<int32_t>(threadIdx.x);
-    if (p.scale && tid < TO / 4)
+    if (p.scale && tid < TO / 4 && o0 + 4 * tid < p.O)
       *reinterpret_cast<f32x4_t*>(&sb[0][4 * tid]) = *reinterpret_cast<const f32x4_t*>(p.scale + o0 + 4 * tid);
-    if (p.bias && tid >= TO / 4 && tid < TO / 2)
+    if (p.bias && tid >= TO / 4 && tid < TO / 2 && o0 + 4 * tid - TO < p.O)
       *reinterpret_cast<f32x4_t*>(&sb[1][4 * tid - TO]) =
           *reinterpret_cast<const f32x4_t*>(p.bias + o0 + 4 * tid - TO);
   }
@@ -187,8 +194,13 @@ __global__ __launch_bounds__(kThreads) void split_k_kernel(KParams p) {
     const int32_t tid = static_cast<int32_t>(threadIdx.x);
     for (int32_t q = tid; q < nel / 8; q += kThreads)
       *reinterpret_cast<u32x4_t*>(wlds + 16 * q) = *reinterpret_cast<const u32x4_t*>(p.vals + e0 + 8 * q);
-    for (int32_t q = tid; q < nel / 16; q += kThreads)
-      *reinterpret_cast<u32x4_t*>(wlds + 2 * nel + 16 * q) = *reinterpret_cast<const u32x4_t*>(p.idx + e0 + 16 * q);
+    if (p.C % 16 == 0) {
+      for (int32_t q = tid; q < nel / 16; q += kThreads)
+        *reinterpret_cast<u32x4_t*>(wlds + 2 * nel + 16 * q) = *reinterpret_cast<const u32x4_t*>(p.idx + e0 + 16 * q);
+    } else {  // rows of 8-byte units
+      for (int32_t q = tid; q < nel / 8; q += kThreads)
+        *reinterpret_cast<u32x2_t*>(wlds + 2 * nel + 8 * q) = *reinterpret_cast<const u32x2_t*>(p.idx + e0 + 8 * q);
+    }
     __syncthreads();
   }
   while (true) {
@@ -196,7 +208,11 @@ __global__ __launch_bounds__(kThreads) void split_k_kernel(KParams p) {
     for (int j = 0; j < U; ++j) {
       const int32_t s = s0 + kWaves * j;
       if (s < nks) {
-        const int32_t c0 = 32 * s + 8 * lq;
+        const int32_t c0 = lane_c0(s);
+        if (s == s_rag) {
+#pragma unroll
+          for (int r = 0; r < RF; ++r) st[j].x[r] = lane_in ? st[j].x[r] : u32x4_t{0u, 0u, 0u, 0u};
+        }
 #pragma unroll
         for (int f = 0; f < OF; ++f) {
           u32x4_t a = u32x4_t{0u, 0u, 0u, 0u};
@@ -217,6 +233,7 @@ __global__ __launch_bounds__(kThreads) void split_k_kernel(KParams p) {
 #pragma unroll
             for (int d = 0; d < 4; ++d) a[d] |= v[d] & m[d];
           }
+          if (s == s_rag) a = lane_in ? a : u32x4_t{0u, 0u, 0u, 0u};
           const bf16x8_t av = __builtin_bit_cast(bf16x8_t, a);
 #pragma unroll
           for (int r = 0; r < RF; ++r)
@@ -257,7 +274,7 @@ __global__ __launch_bounds__(kThreads) void split_k_kernel(KParams p) {
   if (tid >= TR * kPerRow) return;
   const int32_t nl = tid / kPerRow, ol = (tid % kPerRow) * 8;
   const int32_t n = n0 + nl, o = o0 + ol;
-  if (n >= p.N) return;
+  if (n >= p.N || o >= p.O) return;  // (O % 8 == 0: all 8 outputs or none)
   float y[8];
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
@@ -392,10 +409,11 @@ static void split_k_tile(int64_t N, int64_t C, int64_t O, int32_t G, int32_t K, 
   double best = 1e300;
   rf = 2;
   of = 1;
-  const int64_t per_wave = (C / 32 + kWaves - 1) / kWaves;
+  const int64_t per_wave = ((C + 31) / 32 + kWaves - 1) / kWaves;
   for (const auto& c : cand) {
-    if (O % (16 * c[1]) != 0 || !tile_fits(c[0], c[1], K)) continue;
-    const int64_t nob = O / (16 * c[1]);
+    // (whole output blocks where O has them; a ragged O pays for its last one)
+    if ((O % 16 == 0 && O % (16 * c[1]) != 0) || !tile_fits(c[0], c[1], K)) continue;
+    const int64_t nob = (O + 16 * c[1] - 1) / (16 * c[1]);
     const int64_t tiles = (N + 16 * c[0] - 1) / (16 * c[0]) * nob;
     const bool wl = red_bytes(c[0], c[1]) + staged_bytes(c[1], C, G, K) <= kLdsMax;
     const int64_t u = batch_steps(c[0], c[1], K, wl);
@@ -412,14 +430,14 @@ static void split_k_tile(int64_t N, int64_t C, int64_t O, int32_t G, int32_t K, 
   }
 }
 
-bool split_k_supports(const ProductArgs& a) {
+bool split_k_takes(const ProductArgs& a) {
   if (a.x_t != DType::BF16 || a.val_t != DType::BF16) return false;
   if (a.G < 1 || a.G > 256 || a.K < 1 || a.K > 4 || a.K > a.G) return false;
   if (a.conv) {
     const ConvGeom& g = a.geom;
     if (g.KH != 1 || g.KW != 1 || g.sh != 1 || g.sw != 1 || g.ph != 0 || g.pw != 0) return false;
   }
-  if (a.N < 1 || a.C < 32 || a.C % 32 != 0 || a.O % 16 != 0) return false;
+  if (a.N < 1 || a.C < 32 || a.C % 8 != 0 || a.O % 8 != 0) return false;
   const auto al = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
   if (!al(a.X) || !al(a.vals) || !al(a.idx) || !al(a.Y) || (a.residual && !al(a.residual))) return false;
   if ((a.scale && !al(a.scale)) || (a.bias && !al(a.bias))) return false;
@@ -428,8 +446,10 @@ bool split_k_supports(const ProductArgs& a) {
   return true;
 }
 
+bool split_k_supports(const ProductArgs& a) { return a.C % 32 == 0 && a.O % 16 == 0 && split_k_takes(a); }
+
 hipError_t launch_split_k(const ProductArgs& a, hipStream_t s) {
-  if (!split_k_supports(a)) return hipErrorInvalidConfiguration;
+  if (!split_k_takes(a)) return hipErrorInvalidConfiguration;
   int32_t rf, of;
   split_k_tile(a.N, a.C, a.O, a.G, a.K, rf, of);
   KParams p{};
@@ -445,7 +465,7 @@ hipError_t launch_split_k(const ProductArgs& a, hipStream_t s) {
   p.O = static_cast<int32_t>(a.O);
   p.G = a.G;
   p.relu = a.relu;
-  p.nob = static_cast<int32_t>(a.O / (16 * of));
+  p.nob = static_cast<int32_t>((a.O + 16 * of - 1) / (16 * of));
   const int64_t tiles = (a.N + 16 * rf - 1) / (16 * rf) * p.nob;
   if (tiles > (int64_t(1) << 30)) return hipErrorInvalidConfiguration;
   p.tiles = static_cast<int32_t>(tiles);

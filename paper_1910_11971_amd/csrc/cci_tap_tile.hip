@@ -47,26 +47,28 @@ typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) void lds_void_t;
 
-constexpr int kThreads = 256;             // four waves
+constexpr int kThreads = 256;             // four waves (one team)
 constexpr int kTP = 128;                  // pixels of a workgroup tile
 constexpr int kCK = 64;                   // reduction columns per chunk (two k-steps)
 constexpr int kXB = kTP * kCK * 2;        // one activation buffer
-// NX activation buffers, then the two weight tiles: 80 KiB with three
-// buffers (two workgroups per CU), 96 KiB with four (one per CU, one chunk
-// more of prefetch)
+// A team's buffers: kNX activation buffers, then two weight tiles (80 KiB
+// with 128-output tiles: two teams per CU, as two workgroups or as one).
 // TO outputs per workgroup tile (128, or 64 for grids that would leave CUs
 // idle): one weight tile is TO x 64 bf16
+constexpr int kNX = 3;
 constexpr int wb_bytes(int to) { return to * kCK * 2; }
-constexpr int lds_bytes(int nx, int to) { return nx * kXB + 2 * wb_bytes(to); }
+constexpr int lds_bytes(int to) { return kNX * kXB + 2 * wb_bytes(to); }
 // epilogue staging: bytes per pixel row of a wave's 64 x TO/2 fp32 block
 constexpr int ep_pitch(int to) { return to / 2 * 4 + 16; }
 constexpr int kMaxTaps = 32;              // taps of one filter (one validity bit each)
-constexpr uint32_t kDeepGrid = 257;       // grids below this run one workgroup per CU
+constexpr uint32_t kPairGrid = 257;       // grids below this run one workgroup per CU: of two teams
+constexpr int kPairChunks = 4;            // and have at least this many chunks
 constexpr int64_t kSmallGrid = 128;       // fewer 128-output tiles than this (half the CUs): 64-output tiles
 constexpr uint32_t kOOB = 0x80000000u;    // buffer offset that reads as zero / drops a store
 constexpr int kRsrcWord3 = 0x00020000;    // raw buffer descriptor word 3 (gfx9 family)
-static_assert(4 * 64 * ep_pitch(128) <= lds_bytes(3, 128) && 4 * 64 * ep_pitch(64) <= lds_bytes(3, 64),
-              "epilogue staging reuses the operand buffers");
+static_assert(4 * 64 * ep_pitch(128) <= lds_bytes(128) && 4 * 64 * ep_pitch(64) <= lds_bytes(64) &&
+                  2 * lds_bytes(128) <= 160 * 1024,
+              "epilogue staging reuses the operand buffers; two teams fit a CU");
 
 struct TParams {
   const uint16_t* X;
@@ -80,6 +82,7 @@ struct TParams {
   int32_t N, C, O, G, K, relu;
   int32_t npb, nob, nch;  // pixel blocks (of 128), output blocks (of TO), chunks
   int32_t cpt;            // chunks per tap: Cin / 64
+  int32_t full, rag_k8;   // whole chunks (C / 64), and the 8-column blocks after them
   int32_t rows_w;         // packed rows behind one wave's TO / 4 tile rows: TO / 4 * K / G
   int32_t grid8;          // launched workgroups / 8 (the tile count rounded up to a multiple of 8)
   int32_t ntiles;         // npb * nob
@@ -157,8 +160,16 @@ __device__ __forceinline__ uint32_t trow(uint32_t o) { return ((o >> 4) << 11) |
 // entry kept, indices ascending, so a unit is one tile row's 16 bytes).
 // BIGG: G == 32 (a group spans two 16-row blocks).  MASK: some lanes have no
 // unit (else the checks compile away).
-template <typename YT, int UPL, bool FULL, bool BIGG, bool MASK, int NX, int TO>
-__device__ __forceinline__ void tap_tile_body(const TParams& p, uint8_t* lds) {
+//
+// KS: teams of four waves in the workgroup.  With two, team h takes the h-th
+// half of the chunks, each team in LDS buffers of its own, and the partial
+// tiles are added at the end: where the grid leaves one workgroup per CU, a
+// SIMD then holds two waves whose LDS latencies, waits and tile builds
+// overlap (the chunk loop of a lone team is bound by them, not by memory:
+// prefetching deeper did not change it).
+template <typename YT, int UPL, bool FULL, bool BIGG, bool MASK, int KS, int TO>
+__device__ __forceinline__ void tap_tile_body(const TParams& p, uint8_t* const lds0) {
+  constexpr int NX = kNX;
   constexpr int RW = NX - 1;         // packed-unit ring stages: W(m) is issued with X(m)
   constexpr int OT = TO / 32;        // 16-output tiles per wave
   constexpr int RPW = TO / 4;        // weight-tile rows a wave builds
@@ -166,8 +177,13 @@ __device__ __forceinline__ void tap_tile_body(const TParams& p, uint8_t* lds) {
   constexpr int PITCH = ep_pitch(TO);
   constexpr int NMF = 4 * OT;        // MFMAs of one k-step
   const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int w = wv & 3, team = KS > 1 ? wv >> 2 : 0;
   const int wp = w >> 1, wo = w & 1;  // pixel half, output half (TO / 2 outputs) of this wave
+  uint8_t* const lds = lds0 + team * lds_bytes(TO);
+  // this team's chunks: nch from chunk ch0 on (both teams run the same number
+  // of steps; a chunk past the reduction is all zeros)
+  const int nch = (p.nch + KS - 1) / KS, ch0 = team * nch;
 
   // ---- tile of this workgroup ---------------------------------------------
   // Dispatch places workgroup b on XCD b % 8; L numbers the workgroups of one
@@ -221,11 +237,25 @@ __device__ __forceinline__ void tap_tile_body(const TParams& p, uint8_t* lds) {
   // kw = column of the tap, off = byte offset of (tap, block) from the
   // pixel's tap-(0, 0) block.  The next block of a tap, and the first block
   // of the next tap in the row, are both 128 bytes further.
-  int cur_t = 0, cur_cb = 0, cur_kw = 0;
-  int32_t cur_off = 0;
+  int cur_t = ch0 / p.cpt, cur_cb = ch0 - cur_t * p.cpt;
+  const int cur_kh = cur_t / p.KW;
+  int cur_kw = cur_t - cur_kh * p.KW;
+  int32_t cur_off = ((cur_kh * p.W + cur_kw) * p.Cin + cur_cb * kCK) * 2;
   const int32_t row_skip = (p.W - p.KW) * p.Cin * 2;
-  auto issue_x = [&](int buf) {
+  // (From chunk `full` on the column blocks past C read zero, in X here and in
+  // the packed rows in load_w, so that a neighbouring row's infinity cannot
+  // meet a zero.)
+  const int rag = p.full - ch0;  // the first chunk of this team that is not whole
+  const auto live_k8 = [&](int ch) { return ch == rag ? p.rag_k8 : 0; };
+  auto issue_x = [&](int ch, int buf) {
     uint8_t* dst = lds + buf * kXB + w * 4096;
+    if (ch >= rag) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int q = (4 * w + i) * 8 + (lane >> 3);
+        xinv[i] = ((lane & 7) ^ ((q >> 1) & 7)) < live_k8(ch) ? xinv[i] : ~0u;
+      }
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const uint32_t off = static_cast<uint32_t>(xbase[i] + cur_off) | (((xinv[i] >> cur_t) & 1u) << 31);
@@ -278,10 +308,14 @@ __device__ __forceinline__ void tap_tile_body(const TParams& p, uint8_t* lds) {
   u32x2_t pi[RW][UPL];
   auto load_w = [&](int ch, auto kc) {
     constexpr int k = decltype(kc)::value;
+    if (ch >= rag && (lane & 7) >= live_k8(ch)) {  // (c8 of every unit of a lane is lane % 8)
+#pragma unroll
+      for (int u = 0; u < UPL; ++u) voff[u] = ioff[u] = kOOB;
+    }
 #pragma unroll
     for (int u = 0; u < UPL; ++u) {
-      pv[k][u] = load_x4(vd, voff[u] + static_cast<uint32_t>(ch) * (kCK * 2));
-      if constexpr (!FULL) pi[k][u] = load_x2(id, ioff[u] + static_cast<uint32_t>(ch) * kCK);
+      pv[k][u] = load_x4(vd, voff[u] + static_cast<uint32_t>(ch0 + ch) * (kCK * 2));
+      if constexpr (!FULL) pi[k][u] = load_x2(id, ioff[u] + static_cast<uint32_t>(ch0 + ch) * kCK);
     }
   };
   auto w_fence = [&](auto kc) { fence_stage<decltype(kc)::value, FULL>(pv, pi); };
@@ -352,7 +386,6 @@ __device__ __forceinline__ void tap_tile_body(const TParams& p, uint8_t* lds) {
   // landed" (and W(j+1) with it) is "at most the pairs issued after it are in
   // flight".
   constexpr int kPair = (FULL ? 1 : 2) * UPL + 4;  // vector-memory operations of one pair
-  const int nch = p.nch;
   auto wait_pairs = [](int n) {  // at most n pairs in flight (n < RW)
     switch (n) {
       case 0: wait_vm<0>(); break;
@@ -366,7 +399,7 @@ __device__ __forceinline__ void tap_tile_body(const TParams& p, uint8_t* lds) {
   for_k(std::make_integer_sequence<int, RW>{}, [&](auto kc) {
     if (decltype(kc)::value < nch) {
       load_w(decltype(kc)::value, kc);
-      issue_x(decltype(kc)::value % NX);
+      issue_x(decltype(kc)::value, decltype(kc)::value % NX);
     }
   });
   wait_pairs(min(RW, nch) - 1);  // W(0), X(0)
@@ -412,7 +445,7 @@ __device__ __forceinline__ void tap_tile_body(const TParams& p, uint8_t* lds) {
         if (i >= NMF / 2 && i < NMF / 2 + RPW / 8 && next) zero_piece(tb, i - NMF / 2);
       }
       if (i == NMF - 4 && issue) load_w(j + RW, kc);
-      if (i == NMF - 3 && issue) issue_x((j + RW) % NX);
+      if (i == NMF - 3 && issue) issue_x(j + RW, (j + RW) % NX);
       __builtin_amdgcn_sched_barrier(0);
     }
     if (next) {
@@ -452,59 +485,90 @@ __device__ __forceinline__ void tap_tile_body(const TParams& p, uint8_t* lds) {
   });
 
   // ---- fused epilogue -----------------------------------------------------------
-  // Each wave parks its 64 pixels x TO/2 outputs (fp32) in its own LDS region
+  // A wave parks its 64 / KS pixels x TO/2 outputs (fp32) in its own LDS region
   // (pitch TO/2 * 4 + 16 bytes: conflict-free both ways) and reads them back
   // by pixel rows: a lane then owns 8 consecutive outputs of one pixel (LPR
   // lanes cover the wave's TO/2), applies scale / bias / residual / ReLU in
   // fp32, rounds once and stores 16 (bf16) or 32 bytes.  (The loop's last
-  // barrier has released the operand buffers.)
+  // barrier has released the operand buffers.)  With two teams, wave w of
+  // team h finishes pixel tiles 2 h, 2 h + 1: it leaves its partial sums of
+  // the other two tiles to wave w of the other team.
   constexpr int LPR = TO / 16;   // lanes per pixel row
-  constexpr int RPP = 64 / LPR;  // rows per pass (LPR passes)
+  constexpr int RPP = 64 / LPR;  // rows per pass
+  constexpr int NPT = 4 / KS;    // pixel tiles this wave finishes
+  constexpr int NPS = LPR / KS;  // its passes
   mfma_drain();  // the last MFMAs have written acc
 #pragma unroll
   for (int pt = 0; pt < 4; ++pt)
 #pragma unroll
     for (int ot = 0; ot < OT; ++ot) acc_fence(acc[pt][ot]);
   constexpr uint32_t ysz = sizeof(YT);
-  uint8_t* stg = lds + w * 64 * PITCH;
+  uint8_t* stg = lds0 + wv * (16 * NPT) * PITCH;
   const __amdgpu_buffer_rsrc_t yr =
       __builtin_amdgcn_make_buffer_rsrc(p.Y, (short)0, static_cast<int>(p.y_bytes), kRsrcWord3);
   const __amdgpu_buffer_rsrc_t rsr = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<void*>(p.residual), (short)0, p.residual ? static_cast<int>(p.y_bytes) : 0, kRsrcWord3);
   const int c8 = lane % LPR;  // 8-output block of the wave's TO/2
   const uint32_t o = ob * TO + static_cast<uint32_t>(wo * (TO / 2) + 8 * c8);
+  const bool o_ok = o < static_cast<uint32_t>(p.O);  // (O % 8 == 0: all of the lane's outputs or none)
   const auto row_off = [&](int rr) {  // Y / residual byte offset of the lane's row rr
-    const uint32_t px = pb * kTP + static_cast<uint32_t>(wp * 64 + RPP * rr + lane / LPR);
-    return px < static_cast<uint32_t>(p.N) ? (px * static_cast<uint32_t>(p.O) + o) * ysz : kOOB;
+    const uint32_t px = pb * kTP + static_cast<uint32_t>(wp * 64 + 16 * NPT * team + RPP * rr + lane / LPR);
+    return px < static_cast<uint32_t>(p.N) && o_ok ? (px * static_cast<uint32_t>(p.O) + o) * ysz : kOOB;
   };
   // bf16 residual: all rows' 16-byte pieces are requested before the
   // accumulators are parked (one load latency, not one per row)
-  u32x4_t rres[LPR];
+  u32x4_t rres[NPS];
   if constexpr (ysz == 2) {
     if (p.residual) {
 #pragma unroll
-      for (int rr = 0; rr < LPR; ++rr)
+      for (int rr = 0; rr < NPS; ++rr)
         rres[rr] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rsr, row_off(rr), 0, 0));
     }
   }
+  const auto slot = [&](uint8_t* region, int q, int ot) {  // block (q, ot) of a region
+    return reinterpret_cast<f32x4_t*>(region + (q * 16 + (lane & 15)) * PITCH + (ot * 16 + 4 * (lane >> 4)) * 4);
+  };
+  if constexpr (KS == 1) {
 #pragma unroll
-  for (int pt = 0; pt < 4; ++pt)
+    for (int pt = 0; pt < 4; ++pt)
 #pragma unroll
-    for (int ot = 0; ot < OT; ++ot)
-      *reinterpret_cast<f32x4_t*>(stg + (pt * 16 + (lane & 15)) * PITCH + (ot * 16 + 4 * (lane >> 4)) * 4) =
-          acc[pt][ot];
+      for (int ot = 0; ot < OT; ++ot) *slot(stg, pt, ot) = acc[pt][ot];
+  } else {
+    // the partner finds this wave's partial sums in its own region and adds
+    // its accumulators to them in place
+    uint8_t* const other = lds0 + (wv ^ 4) * (16 * NPT) * PITCH;
+    for_k(std::make_integer_sequence<int, KS>{}, [&](auto hc) {
+      constexpr int H = decltype(hc)::value;
+      if (team == H) {
+#pragma unroll
+        for (int q = 0; q < NPT; ++q)
+#pragma unroll
+          for (int ot = 0; ot < OT; ++ot) *slot(other, q, ot) = acc[NPT * (1 - H) + q][ot];
+      }
+    });
+    lds_barrier();
+    for_k(std::make_integer_sequence<int, KS>{}, [&](auto hc) {
+      constexpr int H = decltype(hc)::value;
+      if (team == H) {
+#pragma unroll
+        for (int q = 0; q < NPT; ++q)
+#pragma unroll
+          for (int ot = 0; ot < OT; ++ot) *slot(stg, q, ot) += acc[NPT * H + q][ot];
+      }
+    });
+  }
   f32x4_t sc0{1.f, 1.f, 1.f, 1.f}, sc1{1.f, 1.f, 1.f, 1.f}, bi0{0.f, 0.f, 0.f, 0.f}, bi1{0.f, 0.f, 0.f, 0.f};
-  if (p.scale) {
+  if (p.scale && o_ok) {
     sc0 = *reinterpret_cast<const f32x4_t*>(p.scale + o);
     sc1 = *reinterpret_cast<const f32x4_t*>(p.scale + o + 4);
   }
-  if (p.bias) {
+  if (p.bias && o_ok) {
     bi0 = *reinterpret_cast<const f32x4_t*>(p.bias + o);
     bi1 = *reinterpret_cast<const f32x4_t*>(p.bias + o + 4);
   }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this wave's staging writes have landed
 #pragma unroll
-  for (int rr = 0; rr < LPR; ++rr) {
+  for (int rr = 0; rr < NPS; ++rr) {
     const int row = RPP * rr + lane / LPR;
     const uint8_t* src = stg + row * PITCH + c8 * 32;
     f32x4_t y0 = *reinterpret_cast<const f32x4_t*>(src);
@@ -552,30 +616,35 @@ __device__ __forceinline__ void tap_tile_body(const TParams& p, uint8_t* lds) {
   }
 }
 
-template <typename YT, int UPL, bool FULL, bool BIGG, bool MASK, int NX, int TO>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NX == 3 ? 2 : 1, NX == 3 ? 2 : 1)))
+template <typename YT, int UPL, bool FULL, bool BIGG, bool MASK, int KS, int TO>
+__global__ __launch_bounds__(kThreads * KS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void tap_tile_kernel(TParams p) {
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-  tap_tile_body<YT, UPL, FULL, BIGG, MASK, NX, TO>(p, lds);
+  tap_tile_body<YT, UPL, FULL, BIGG, MASK, KS, TO>(p, lds);
 }
 
-template <typename YT, int UPL, bool FULL, bool BIGG, bool MASK, int NX, int TO>
+template <typename YT, int UPL, bool FULL, bool BIGG, bool MASK, int KS, int TO>
 hipError_t launch_tn(const TParams& p, hipStream_t s) {
   static std::atomic<int8_t> lds_set[kMaxDevices];
-  const hipError_t attr = set_lds_limit_once(
-      lds_set, reinterpret_cast<const void*>(&tap_tile_kernel<YT, UPL, FULL, BIGG, MASK, NX, TO>), lds_bytes(NX, TO));
+  const hipError_t attr =
+      set_lds_limit_once(lds_set, reinterpret_cast<const void*>(&tap_tile_kernel<YT, UPL, FULL, BIGG, MASK, KS, TO>),
+                         KS * lds_bytes(TO));
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL((tap_tile_kernel<YT, UPL, FULL, BIGG, MASK, NX, TO>), dim3(8u * static_cast<uint32_t>(p.grid8)),
-                     dim3(kThreads), lds_bytes(NX, TO), s, p);
+  hipLaunchKernelGGL((tap_tile_kernel<YT, UPL, FULL, BIGG, MASK, KS, TO>), dim3(8u * static_cast<uint32_t>(p.grid8)),
+                     dim3(kThreads * KS), KS * lds_bytes(TO), s, p);
   return hipGetLastError();
 }
 
-// Two workgroups per CU once the grid covers every CU twice; below that,
-// one per CU with the deeper prefetch.
+// Two one-team workgroups per CU once the grid covers every CU twice; below
+// that one workgroup of two teams, if each has a few chunks (us, one team
+// with a fourth activation buffer / two teams: 12544 x 1024 -> 256 18.5 /
+// 16.3; 3136 x 4608 -> 512 44 / 36; 1537 x 2048 -> 1000 25.4 / 21.0; 300 x
+// 4096 -> 4096 43.4 / 33.6).
 template <typename YT, int UPL, bool FULL, bool BIGG, bool MASK, int TO>
 hipError_t launch_tu(const TParams& p, hipStream_t s) {
-  return static_cast<uint32_t>(p.ntiles) >= kDeepGrid ? launch_tn<YT, UPL, FULL, BIGG, MASK, 3, TO>(p, s)
-                                                       : launch_tn<YT, UPL, FULL, BIGG, MASK, 4, TO>(p, s);
+  return static_cast<uint32_t>(p.ntiles) >= kPairGrid || p.nch < kPairChunks
+             ? launch_tn<YT, UPL, FULL, BIGG, MASK, 1, TO>(p, s)
+             : launch_tn<YT, UPL, FULL, BIGG, MASK, 2, TO>(p, s);
 }
 
 template <typename YT, bool BIGG, int TO>
@@ -603,17 +672,19 @@ hipError_t launch_ty(const TParams& p, hipStream_t s, int to) {
 
 }  // namespace
 
-bool tap_tile_supports(const ProductArgs& a) {
+bool tap_tile_takes(const ProductArgs& a) {
   if (a.x_t != DType::BF16 || a.val_t != DType::BF16) return false;
   if (a.G < 1 || a.G > 32 || 32 % a.G != 0 || a.K < 1 || a.K > a.G) return false;
   // at most half of each group kept, or all of it (dense control): above
   // that the packed units no longer fit the registers beside the rings
   if (2 * a.K > a.G && a.K != a.G) return false;
-  // O % 128 (tiles of 128 outputs), or O % 64 with G <= 16 (tiles of 64: a
-  // group must fit one wave's 16 rows)
-  if (a.N < 1 || a.O % 64 != 0 || (a.O % 128 != 0 && a.G > 16)) return false;
+  // a lane of the epilogue holds 8 outputs; G = 32 takes whole tiles of 128
+  // outputs only (a group must fit the rows one wave builds)
+  if (a.N < 1 || a.O % 8 != 0 || (a.O % 128 != 0 && a.G > 16)) return false;
+  // chunks of 64 columns under one tap; the last chunk of a single tap's
+  // reduction may be short (in blocks of 8 columns)
   const int64_t cin = a.conv ? a.geom.Cin : a.C;
-  if (cin % kCK != 0) return false;
+  if (cin % kCK != 0 && (cin != a.C || cin % 8 != 0)) return false;
   if (a.conv && a.geom.KH * a.geom.KW > kMaxTaps) return false;
   const auto al = [](const void* q, uintptr_t m) { return (reinterpret_cast<uintptr_t>(q) & (m - 1)) == 0; };
   if (!al(a.X, 16) || !al(a.vals, 16) || !al(a.idx, 8) || !al(a.Y, 16)) return false;
@@ -627,8 +698,13 @@ bool tap_tile_supports(const ProductArgs& a) {
   return true;
 }
 
+bool tap_tile_supports(const ProductArgs& a) {
+  const int64_t cin = a.conv ? a.geom.Cin : a.C;
+  return cin % kCK == 0 && a.O % 64 == 0 && tap_tile_takes(a);
+}
+
 hipError_t launch_tap_tile(const ProductArgs& a, hipStream_t s) {
-  if (!tap_tile_supports(a)) return hipErrorInvalidConfiguration;
+  if (!tap_tile_takes(a)) return hipErrorInvalidConfiguration;
   TParams p{};
   p.X = static_cast<const uint16_t*>(a.X);
   p.vals = static_cast<const uint16_t*>(a.vals);
@@ -672,15 +748,19 @@ hipError_t launch_tap_tile(const ProductArgs& a, hipStream_t s) {
   p.K = a.K;
   p.relu = a.relu;
   p.npb = static_cast<int32_t>((a.N + kTP - 1) / kTP);
-  // 128-output tiles, unless O is not a multiple of 128 or they would leave
-  // more than half of the CUs idle and 64-output ones are possible (measured:
-  // 3136 x 4608 x 512, 100 tiles, 51 -> 44 us; at 196 tiles the 64-output
-  // plan is 10-15% slower)
-  const int64_t grid128 = a.O % 128 == 0 ? static_cast<int64_t>(p.npb) * (a.O / 128) : 0;
-  const int to = a.O % 128 == 0 && (grid128 >= kSmallGrid || a.G > 16) ? 128 : 64;
-  p.nob = static_cast<int32_t>(a.O / to);
-  p.nch = static_cast<int32_t>(a.C / kCK);
-  p.cpt = p.Cin / kCK;
+  // 128-output tiles, unless they would leave more than half of the CUs idle
+  // or one of them would be more than half empty (us, 128 / 64 outputs:
+  // 12544 x 1024 -> 256, 196 tiles, 16.3 / 19.9; 12544 x 816 -> 136, 196
+  // tiles, 15.6 / 17.4; 1537 x 2048 -> 1000, 104 tiles, 23.2 / 20.0; 12544 x
+  // 576 -> 96, 98 tiles, 12.7 / 10.6; 50176 x 288 -> 48 14.5 / 12.3).
+  // G = 32 has no 64-output form.
+  const int64_t grid128 = static_cast<int64_t>(p.npb) * ((a.O + 127) / 128);
+  const int to = a.G > 16 || (grid128 >= kSmallGrid && a.O > 64) ? 128 : 64;
+  p.nob = static_cast<int32_t>((a.O + to - 1) / to);
+  p.nch = static_cast<int32_t>((a.C + kCK - 1) / kCK);
+  p.cpt = (p.Cin + kCK - 1) / kCK;
+  p.full = static_cast<int32_t>(a.C / kCK);
+  p.rag_k8 = static_cast<int32_t>(a.C % kCK / 8);
   p.rows_w = to / 4 * a.K / a.G;
   const int64_t grid = static_cast<int64_t>(p.npb) * p.nob;
   if (grid > 0x7fffffff) return hipErrorInvalidConfiguration;

@@ -226,6 +226,20 @@ def test_conv_tap_tile_epilogue(y_dtype):
              "tap_tile_mfma", ep=ep)
 
 
+@pytest.mark.parametrize("B,H,W,Cin,O,k,stride,pad,G,K", [
+    (9, 30, 30, 64, 64, 3, 2, 1, 8, 2), (20, 28, 28, 64, 96, 3, 1, 1, 8, 2),  # 64- and 96-output tiles, taps
+    (40, 17, 19, 136, 72, 1, 2, 0, 8, 4), (8, 30, 31, 72, 200, 1, 1, 1, 8, 2),  # strided / padded 1x1, short chunk
+    (3, 14, 14, 256, 256, 3, 1, 1, 8, 2), (2, 9, 9, 64, 136, 5, 1, 2, 8, 4),  # two teams starting inside a filter row
+])
+def test_conv_ragged_auto(B, H, W, Cin, O, k, stride, pad, G, K):
+    """Convolutions AUTO gives to the tap-chunk and split-reduction kernels' ragged forms."""
+    need_gpu()
+    Ho, Wo = (H + 2 * pad - k) // stride + 1, (W + 2 * pad - k) // stride + 1
+    ep = rand_epilogue(O, B * Ho * Wo, torch.bfloat16, 131 + Cin, residual=True, relu=True)
+    run_conv(rand_x((B, H, W, Cin), torch.bfloat16, 132 + O), rand_w(O, k * k * Cin, 133 + G), G, K, k, stride, pad,
+             torch.bfloat16, "auto", ep=ep)
+
+
 def test_conv_tap_tile_refuses_unsupported():
     """Cin % 64 != 0, O % 64 != 0, G = 64, and G = 32 with O % 128 != 0 are refused by the tap-chunk family."""
     need_gpu()

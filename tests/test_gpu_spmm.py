@@ -115,6 +115,47 @@ def test_spmm_bf16_tap_tile(N, C, O, G, K):
     run_case(rand_x(N, C, torch.bfloat16, N + C), rand_w(O, C, O + G), G, K, torch.bfloat16, "tap_tile_mfma")
 
 
+RAGGED_CASES = [  # N, C, O, G, K: products AUTO gives to the tap-chunk and split-reduction kernels' ragged forms
+    # tap-chunk: 1, 7 and 0 column blocks in the last chunk, 8 outputs in the last tile, both tile widths
+    (6000, 136, 816, 8, 2), (9000, 824, 136, 8, 4), (5000, 120, 72, 8, 1), (20000, 104, 264, 8, 3),
+    (3000, 1336, 520, 4, 2), (2500, 96, 1000, 8, 8), (2000, 2040, 1000, 8, 2), (9001, 200, 24, 2, 1),
+    (6000, 136, 256, 32, 7),
+    # two teams: an odd number of chunks (the second team's last one is empty), a short chunk before it
+    (300, 320, 1008, 16, 8), (300, 1480, 1008, 16, 16), (257, 264, 1032, 8, 8), (40, 1040, 2056, 8, 8),
+    # split-reduction: 8, 16 and 24 columns in the last k-step, rows of 8-byte index units, 8 outputs in the last tile
+    (49, 1352, 232, 8, 2), (130, 72, 40, 8, 1), (65, 88, 24, 4, 2), (300, 1000, 136, 8, 4), (33, 2072, 56, 8, 3),
+    (100, 5000, 48, 16, 4), (70, 1016, 320, 64, 2),
+]
+
+
+@pytest.mark.parametrize("N,C,O,G,K", RAGGED_CASES)
+def test_spmm_bf16_ragged_auto(N, C, O, G, K):
+    need_gpu()
+    ep = rand_epilogue(O, N, torch.bfloat16, N + O, residual=N % 2 == 0, relu=True)
+    run_case(rand_x(N, C, torch.bfloat16, N + C), rand_w(O, C, O + G), G, K, torch.bfloat16, "auto", ep=ep)
+    run_case(rand_x(N, C, torch.bfloat16, N + C), rand_w(O, C, O + G), G, K, torch.float32, "auto")
+
+
+@pytest.mark.parametrize("N,C,O", [(3000, 136, 136), (130, 72, 48)])  # tap-chunk, split-reduction
+def test_spmm_ragged_reduction_keeps_neighbours_out(N, C, O):
+    """The columns past a ragged reduction are another packed row's (here all infinite) and X's next row: neither may
+    reach this row's sums."""
+    need_gpu()
+    from paper_1910_11971_amd import cci
+    G, K = 8, 2
+    W = rand_w(O, C, 5)
+    vals, idx = cci.pack(torch.from_numpy(W).to(DEV), G, K, torch.bfloat16)
+    ref = cci.spmm(rand_x(N, C, torch.bfloat16, 6).to(DEV), vals, idx, G, algo="narrow_mfma")
+    vals[1::2] = float("inf")
+    X = rand_x(N, C, torch.bfloat16, 6).to(DEV)
+    X[1::2] = float("nan")
+    Y = cci.spmm(X, vals, idx, G)
+    even = Y.view(N, O // G, G)[0::2, 0::2].float()
+    want = ref.view(N, O // G, G)[0::2, 0::2].float()
+    assert torch.isfinite(even).all()
+    assert (even - want).abs().max() <= 1e-2 * want.abs().max()
+
+
 STREAM_FC_CASES = [  # N, C, O, G, K: FC products on the streaming kernels (C <= 256)
     (1, 64, 64, 8, 2), (127, 128, 128, 16, 4), (128, 64, 128, 8, 8), (129, 192, 256, 32, 5),
     (1000, 256, 320, 4, 1), (5000, 192, 192, 2, 2), (3000, 256, 128, 1, 1), (777, 128, 384, 32, 32),
