@@ -8,21 +8,25 @@
 //
 // Few-row product (N <= 64).  With few rows every packed weight is used by
 // at most N multiply-adds, so the packed bytes (2 per value + b/8 per index)
-// set the time.  A workgroup of eight waves owns 16 output channels (the
-// last one fewer when O % 16 != 0: its missing rows stay zero and are not
-// stored); wave w
-// takes the 32-column k-steps w, w+8, ... of the reduction.  Per k-step a wave
-//   - clears its 16 x 32 bf16 tile in LDS (one 16-byte store per lane),
-//   - reads the kept entries of the groups covering its 16 rows (lanes over
-//     the 32 columns, so values and index bits are read contiguously),
-//     decodes each index from the stream, and writes every value whose row
-//     falls in the tile to (row, column) -- Alg. 1's routing to row gG+idx,
-//   - reads the tile back as the A fragment of v_mfma_f32_16x16x32_bf16 and
-//     multiplies it with up to four 16-row fragments of X.
-// The eight waves' partial sums are added in LDS; the fused epilogue and one
-// rounding follow.  The tile stores unit u (8 columns) of row i at
-// (u ^ ((i >> 2) & 3)) * 16 + i * 64, so a fragment read touches distinct
-// 16-byte bank slots within every quarter-wave.
+// and the memory latency set the time.  A workgroup of eight waves owns 16
+// output channels (the last one fewer when O % 16 != 0: its missing rows are
+// not stored); wave w takes the 128-column chunks w, w+8, ... of the
+// reduction and keeps the loads of up to four of them in flight, so a
+// reduction of 4096 costs about one memory round trip (with one 32-column
+// k-step in flight and 2-byte loads it cost sixteen: 1 x 4096 -> 4096, G = 16,
+// K = 4, 11.3 us of kernel time against 8.0 now).  Per chunk a wave
+//   - clears its 16 x 128 bf16 tile in LDS,
+//   - reads the kept entries of the groups covering its 16 rows in units of 8
+//     columns of one packed row (16 bytes of values, 8 index entries: b
+//     bytes), and writes every value whose row falls in the tile to (row,
+//     column) -- Alg. 1's routing to row gG+idx; with K == G the slots are the
+//     rows and a unit is stored whole,
+//   - reads the tile back as A fragments of v_mfma_f32_16x16x32_bf16 and
+//     multiplies them with up to four 16-row fragments of X.
+// The eight waves' partial sums are added in LDS; the fused epilogue (its
+// operands requested before the reduction) and one rounding follow.  Tile
+// row i keeps its 16-byte unit u at 256 i + 16 (u ^ i): the 16 rows of a
+// fragment read touch distinct bank slots.
 #include <algorithm>
 #include <type_traits>
 
@@ -74,40 +78,40 @@ struct FParams {
   int32_t N, C, O, G, K, b, relu;
 };
 
-// Loads of one k-step: up to PL kept entries per lane (index word(s) and
-// value) and the lane's X fragments.
+constexpr int kCW = 128;                 // columns of a chunk
+constexpr int kTileB = 16 * kCW * 2;     // bytes of a wave's tile
+
+// Loads of one chunk: up to PL packed units per lane (values and index
+// words) and the lane's X fragments.
 template <int PL, int NB>
 struct Fetch {
-  uint32_t lo[PL > 0 ? PL : 1], hi[PL > 0 ? PL : 1];
-  uint16_t v[PL > 0 ? PL : 1];
-  u32x4_t x[NB];
+  u32x4_t v[PL];
+  uint32_t ix[PL][3];
+  u32x4_t x[4][NB];
 };
 
-template <int NB, int PL, typename YT>
+// Chunks in flight per wave: as many as fit about 170 registers, at most 4.
+constexpr int depth(int pl, int nb) {
+  const int d = 170 / (pl * 7 + nb * 16);
+  return d < 1 ? 1 : d > 4 ? 4 : d;
+}
+
+// PL: packed units per lane and pass; ONE: one pass covers a chunk (else the
+// units of a chunk are walked in passes, loaded inline).
+template <int NB, int PL, bool ONE, typename YT>
 __global__ __launch_bounds__(kFThreads) void spmm_bits_kernel(FParams p) {
-  __shared__ __attribute__((aligned(16))) uint8_t tiles[kFWaves][1024];
+  constexpr int D = ONE ? depth(PL, NB) : 1;
+  __shared__ __attribute__((aligned(16))) uint8_t tiles[kFWaves][kTileB];
   __shared__ __attribute__((aligned(16))) f32x4_t red[kFWaves][NB][64];
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int32_t o0 = static_cast<int32_t>(blockIdx.x) * 16;
   const int32_t g_lo = o0 / p.G, g_hi = min((o0 + 15) / p.G, p.O / p.G - 1);
-  // (group, slot) pairs cover the k-step's 32 columns: lanes 0..31 take the
-  // even pairs, lanes 32..63 the odd ones, lane & 31 the column; entry u of
-  // a lane is pair pk + 2u, at packed offset base[u] + 32 s in k-step s
-  const int32_t npairs = (g_hi - g_lo + 1) * p.K;
-  const int32_t pk = lane >> 5, cj = lane & 31;
-  constexpr int PA = PL > 0 ? PL : 1;
-  int64_t base[PA];
-  int32_t row0[PA];
-  bool on[PA];
-#pragma unroll
-  for (int u = 0; u < PL; ++u) {
-    const int32_t q = pk + 2 * u;
-    on[u] = q < npairs;
-    const int32_t gl = on[u] ? q / p.K : 0, k = on[u] ? q - gl * p.K : 0;
-    base[u] = (static_cast<int64_t>(g_lo + gl) * p.K + k) * p.C + cj;
-    row0[u] = (g_lo + gl) * p.G - o0;
-  }
+  // packed rows (group, slot) x 16 units of a chunk: lane & 15 is the unit
+  // (8 columns), entry u of a lane packed row lane / 16 + 4 u
+  const int32_t nrows = (g_hi - g_lo + 1) * p.K;
+  const int32_t c8 = lane & 15, r4 = lane >> 4;
+  const bool full = p.K == p.G;
 
   const __amdgpu_buffer_rsrc_t xr =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.X), (short)0, static_cast<int>(p.x_bytes), kRsrcWord3);
@@ -115,103 +119,142 @@ __global__ __launch_bounds__(kFThreads) void spmm_bits_kernel(FParams p) {
       __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.idx), (short)0, static_cast<int>(p.i_bytes), kRsrcWord3);
   const __amdgpu_buffer_rsrc_t vr =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.vals), (short)0, static_cast<int>(p.v_bytes), kRsrcWord3);
-  const uint32_t mask = (1u << p.b) - 1u;
+  constexpr uint32_t kOut = 0x80000000u;  // reads as zero
   uint8_t* tile = tiles[w];
   const int ti = lane & 15, tq = lane >> 4;
-  const uint8_t* frag = tile + ti * 64 + ((tq ^ ((ti >> 2) & 3)) * 16);
 
-  auto fetch = [&](int32_t s, Fetch<PL, NB>& f) {
-    const int32_t c0 = s * 32;
-#pragma unroll
-    for (int u = 0; u < PL; ++u) {
-      const int64_t e = base[u] + c0;
-      const uint32_t voff = on[u] ? static_cast<uint32_t>(e) * 2u : 0x80000000u;
-      f.v[u] = __builtin_amdgcn_raw_buffer_load_b16(vr, voff, 0, 0);
-      if (p.b == 8) {
-        f.lo[u] = __builtin_amdgcn_raw_buffer_load_b8(ir, on[u] ? static_cast<uint32_t>(e) : 0x80000000u, 0, 0);
-        f.hi[u] = 0;
+  // scale, bias and residual of the outputs this wave finishes (rows 16 w ..)
+  const int32_t en = 16 * w + ti, eo = o0 + 4 * tq;
+  const bool eok = w < NB && en < p.N && eo < p.O;  // (O % 4 == 0: a lane's 4 outputs are all inside or all past O)
+  const bool yf32 = std::is_same<YT, float>::value;
+  const int64_t yo = static_cast<int64_t>(en) * p.O + eo;
+  f32x4_t sc{1.f, 1.f, 1.f, 1.f}, bi{0.f, 0.f, 0.f, 0.f}, rs{0.f, 0.f, 0.f, 0.f};
+  if (eok) {
+    if (p.scale) sc = *reinterpret_cast<const f32x4_t*>(p.scale + eo);
+    if (p.bias) bi = *reinterpret_cast<const f32x4_t*>(p.bias + eo);
+    if (p.residual) {
+      if (yf32) {
+        rs = *reinterpret_cast<const f32x4_t*>(static_cast<const float*>(p.residual) + yo);
       } else {
-        const uint32_t off = on[u] ? static_cast<uint32_t>((e * p.b) >> 5) * 4u : 0x80000000u;
-        f.lo[u] = __builtin_amdgcn_raw_buffer_load_b32(ir, off, 0, 0);
-        f.hi[u] = __builtin_amdgcn_raw_buffer_load_b32(ir, on[u] ? off + 4u : 0x80000000u, 0, 0);
+        const u16x4_t r = *reinterpret_cast<const u16x4_t*>(static_cast<const uint16_t*>(p.residual) + yo);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) rs[e] = bf16_to_f32(r[e]);
+      }
+    }
+  }
+
+  // first packed element of this lane's unit of packed row r in chunk 0
+  const auto unit_e = [&](int32_t r) { return (static_cast<int64_t>(g_lo) * p.K + r) * p.C + 8 * c8; };
+  auto load_unit = [&](int64_t e, bool on, u32x4_t& v, uint32_t (&ix)[3]) {
+    v = __builtin_bit_cast(u32x4_t,
+                           __builtin_amdgcn_raw_buffer_load_b128(vr, on ? static_cast<uint32_t>(e) * 2u : kOut, 0, 0));
+    if (full) return;
+    // 8 entries of b bits start at byte e b / 8 (e % 8 == 0): the words that
+    // hold them (b = 7 can straddle three)
+    const uint32_t off = static_cast<uint32_t>((e * p.b) >> 5) * 4u;
+    ix[0] = __builtin_amdgcn_raw_buffer_load_b32(ir, on ? off : kOut, 0, 0);
+    ix[1] = __builtin_amdgcn_raw_buffer_load_b32(ir, on ? off + 4u : kOut, 0, 0);
+    ix[2] = p.b == 7 ? __builtin_amdgcn_raw_buffer_load_b32(ir, on ? off + 8u : kOut, 0, 0) : 0u;
+  };
+  // route a unit of packed row r (its first element e) to the tile
+  auto scatter = [&](int32_t r, int64_t e, const u32x4_t v, const uint32_t (&ix)[3]) {
+    const int32_t gl = r / p.K;
+    const int32_t row0 = (g_lo + gl) * p.G - o0;
+    if (full) {
+      const int32_t row = row0 + r - gl * p.K;
+      if (r < nrows && row >= 0 && row < 16)
+        *reinterpret_cast<u32x4_t*>(tile + row * 256 + ((c8 ^ row) * 16)) = v;
+      return;
+    }
+    const uint32_t sh = static_cast<uint32_t>((e * p.b) & 31);
+    const uint64_t bits = static_cast<uint64_t>(__builtin_amdgcn_alignbit(ix[1], ix[0], sh)) |
+                          (static_cast<uint64_t>(__builtin_amdgcn_alignbit(ix[2], ix[1], sh)) << 32);
+    const uint32_t mask = (1u << p.b) - 1u;
+    if (r < nrows) {
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const int32_t row = row0 + static_cast<int32_t>(static_cast<uint32_t>(bits >> (t * p.b)) & mask);
+        if (row >= 0 && row < 16)
+          *reinterpret_cast<uint16_t*>(tile + row * 256 + ((c8 ^ row) * 16) + 2 * t) =
+              static_cast<uint16_t>(v[t >> 1] >> (16 * (t & 1)));
+      }
+    }
+  };
+  auto clear = [&]() {
+    if (full) return;
+#pragma unroll
+    for (int q = 0; q < kTileB / 1024; ++q)
+      *reinterpret_cast<u32x4_t*>(tile + q * 1024 + lane * 16) = u32x4_t{0u, 0u, 0u, 0u};
+  };
+
+  auto fetch = [&](int32_t ch, Fetch<PL, NB>& f) {
+    const int32_t c0 = ch * kCW;
+    if constexpr (ONE) {
+#pragma unroll
+      for (int u = 0; u < PL; ++u) {
+        const int32_t r = r4 + 4 * u;
+        load_unit(unit_e(r) + c0, r < nrows && c0 + 8 * c8 < p.C, f.v[u], f.ix[u]);
       }
     }
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      const uint32_t n = static_cast<uint32_t>(16 * nb + ti);
-      const uint32_t off = n < static_cast<uint32_t>(p.N)
-                               ? (n * static_cast<uint32_t>(p.C) + static_cast<uint32_t>(c0 + 8 * tq)) * 2u
-                               : 0x80000000u;
-      f.x[nb] = __builtin_amdgcn_raw_buffer_load_b128(xr, off, 0, 0);
-    }
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const uint32_t n = static_cast<uint32_t>(16 * nb + ti);
+        const int32_t c = c0 + 32 * j + 8 * tq;
+        const uint32_t off = n < static_cast<uint32_t>(p.N) && c < p.C
+                                 ? (n * static_cast<uint32_t>(p.C) + static_cast<uint32_t>(c)) * 2u
+                                 : kOut;
+        f.x[j][nb] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(xr, off, 0, 0));
+      }
   };
 
   f32x4_t acc[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) acc[nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  const int32_t nks = p.C / 32;
-  if constexpr (PL == 0) {
-    // many entries per lane (large G x K): walk the pairs with loads inline
-    const int32_t gl0 = pk / p.K, k0 = pk - gl0 * p.K;
-    for (int32_t s = w; s < nks; s += kFWaves) {
-      const int32_t c0 = s * 32;
-      *reinterpret_cast<u32x4_t*>(tile + lane * 16) = u32x4_t{0u, 0u, 0u, 0u};
-      int32_t gl = gl0, k = k0;
-      for (int32_t q = pk; q < npairs; q += 2) {
-        const int64_t e = (static_cast<int64_t>(g_lo + gl) * p.K + k) * p.C + c0 + cj;
-        uint32_t r;
-        if (p.b == 8) {
-          r = __builtin_amdgcn_raw_buffer_load_b8(ir, static_cast<uint32_t>(e), 0, 0);
+  const int32_t nch = (p.C + kCW - 1) / kCW;
+  Fetch<PL, NB> st[D];
+#pragma unroll
+  for (int d = 0; d < D; ++d)
+    if (w + kFWaves * d < nch) fetch(w + kFWaves * d, st[d]);
+  for (int32_t base = w; base < nch; base += kFWaves * D) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      const int32_t ch = base + kFWaves * d;
+      if (ch < nch) {
+        const int32_t c0 = ch * kCW;
+        clear();
+        if constexpr (ONE) {
+#pragma unroll
+          for (int u = 0; u < PL; ++u) scatter(r4 + 4 * u, unit_e(r4 + 4 * u) + c0, st[d].v[u], st[d].ix[u]);
         } else {
-          const uint32_t off = static_cast<uint32_t>((e * p.b) >> 5) * 4u;
-          const uint32_t lo = __builtin_amdgcn_raw_buffer_load_b32(ir, off, 0, 0);
-          const uint32_t hi = __builtin_amdgcn_raw_buffer_load_b32(ir, off + 4u, 0, 0);
-          r = __builtin_amdgcn_alignbit(hi, lo, static_cast<uint32_t>((e * p.b) & 31)) & mask;
-        }
-        const int32_t row = (g_lo + gl) * p.G + static_cast<int32_t>(r) - o0;
-        if (row >= 0 && row < 16)
-          *reinterpret_cast<uint16_t*>(tile + row * 64 + (((cj >> 3) ^ ((row >> 2) & 3)) * 16) + (cj & 7) * 2) =
-              p.vals[e];
-        k += 2;
-        while (k >= p.K) {
-          k -= p.K;
-          ++gl;
-        }
-      }
-      const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(frag);
+#pragma unroll 1
+          for (int32_t r0 = 0; r0 < nrows; r0 += 4 * PL) {
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const uint32_t n = static_cast<uint32_t>(16 * nb + ti);
-        const uint32_t off = n < static_cast<uint32_t>(p.N)
-                                 ? (n * static_cast<uint32_t>(p.C) + static_cast<uint32_t>(c0 + 8 * tq)) * 2u
-                                 : 0x80000000u;
-        const u32x4_t xv = __builtin_amdgcn_raw_buffer_load_b128(xr, off, 0, 0);
-        acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8_t, xv), acc[nb], 0, 0, 0);
+            for (int u = 0; u < PL; ++u) {
+              const int32_t r = r0 + r4 + 4 * u;
+              load_unit(unit_e(r) + c0, r < nrows && c0 + 8 * c8 < p.C, st[d].v[u], st[d].ix[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < PL; ++u) {
+              const int32_t r = r0 + r4 + 4 * u;
+              scatter(r, unit_e(r) + c0, st[d].v[u], st[d].ix[u]);
+            }
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const bf16x8_t a =
+              *reinterpret_cast<const bf16x8_t*>(tile + ti * 256 + (((4 * j + tq) ^ ti) * 16));
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb)
+            acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8_t, st[d].x[j][nb]), acc[nb],
+                                                              0, 0, 0);
+        }
+        if (ch + kFWaves * D < nch) fetch(ch + kFWaves * D, st[d]);
       }
     }
-  } else {
-  Fetch<PL, NB> cur, nxt;
-  if (w < nks) fetch(w, cur);
-  for (int32_t s = w; s < nks; s += kFWaves) {
-    if (s + kFWaves < nks) fetch(s + kFWaves, nxt);
-    const int32_t c0 = s * 32;
-    *reinterpret_cast<u32x4_t*>(tile + lane * 16) = u32x4_t{0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int u = 0; u < PL; ++u) {
-      const int64_t e = base[u] + c0;
-      const uint32_t r = p.b == 8 ? cur.lo[u] : __builtin_amdgcn_alignbit(cur.hi[u], cur.lo[u],
-                                                                          static_cast<uint32_t>((e * p.b) & 31)) & mask;
-      const int32_t row = row0[u] + static_cast<int32_t>(r);
-      if (on[u] && row >= 0 && row < 16)
-        *reinterpret_cast<uint16_t*>(tile + row * 64 + (((cj >> 3) ^ ((row >> 2) & 3)) * 16) + (cj & 7) * 2) = cur.v[u];
-    }
-    const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(frag);
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-      acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8_t, cur.x[nb]), acc[nb], 0, 0, 0);
-    cur = nxt;
-  }
   }
 
   // ---- sum the eight waves' partials; wave nb finishes X rows 16 nb .. +16
@@ -222,24 +265,10 @@ __global__ __launch_bounds__(kFThreads) void spmm_bits_kernel(FParams p) {
   f32x4_t sum = red[0][w][lane];
 #pragma unroll
   for (int v = 1; v < kFWaves; ++v) sum += red[v][w][lane];
-  const int32_t n = 16 * w + ti;
-  const int32_t o = o0 + 4 * tq;  // lane holds outputs o .. o+3 of row n
-  if (n >= p.N || o >= p.O) return;  // (O % 4 == 0: a lane's 4 outputs are all inside or all past O)
-  const bool yf32 = std::is_same<YT, float>::value;
-  const int64_t yo = static_cast<int64_t>(n) * p.O + o;
+  if (!eok) return;
   float y[4];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    y[r] = sum[r];
-    if (p.scale) y[r] *= p.scale[o + r];
-    if (p.bias) y[r] += p.bias[o + r];
-  }
-  if (p.residual) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      y[r] += yf32 ? static_cast<const float*>(p.residual)[yo + r]
-                   : bf16_to_f32(static_cast<const uint16_t*>(p.residual)[yo + r]);
-  }
+  for (int r = 0; r < 4; ++r) y[r] = sum[r] * sc[r] + bi[r] + rs[r];
   if (p.relu) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) y[r] = y[r] > 0.0f ? y[r] : (y[r] != y[r] ? y[r] : 0.0f);
@@ -252,28 +281,27 @@ __global__ __launch_bounds__(kFThreads) void spmm_bits_kernel(FParams p) {
   }
 }
 
-template <int NB, int PL>
+template <int NB, int PL, bool ONE>
 hipError_t launch_fp(const FParams& p, DType y_t, hipStream_t s) {
   const dim3 grid(static_cast<uint32_t>((p.O + 15) / 16));
   if (y_t == DType::F32)
-    hipLaunchKernelGGL((spmm_bits_kernel<NB, PL, float>), grid, dim3(kFThreads), 0, s, p);
+    hipLaunchKernelGGL((spmm_bits_kernel<NB, PL, ONE, float>), grid, dim3(kFThreads), 0, s, p);
   else
-    hipLaunchKernelGGL((spmm_bits_kernel<NB, PL, bf16_t>), grid, dim3(kFThreads), 0, s, p);
+    hipLaunchKernelGGL((spmm_bits_kernel<NB, PL, ONE, bf16_t>), grid, dim3(kFThreads), 0, s, p);
   return hipGetLastError();
 }
 
-// PL: kept entries a lane reads per k-step, ceil(pairs / 2), where pairs =
-// (groups that 16 consecutive rows starting at a multiple of 16 can touch) x K.
-// Up to 8 they are loaded a k-step ahead; beyond, the generic walk.
+// PL: packed units a lane reads per chunk, a quarter of the packed rows of
+// the groups that 16 consecutive outputs starting at a multiple of 16 can
+// touch.  Up to 4 they are loaded chunks ahead; beyond, the walk in passes.
 template <int NB>
 hipError_t launch_f(const FParams& p, DType y_t, hipStream_t s) {
   const int32_t groups = 16 % p.G == 0 ? 16 / p.G : (p.G % 16 == 0 ? 1 : 15 / p.G + 2);
-  const int32_t pl = (groups * p.K + 1) / 2;
-  if (pl <= 1) return launch_fp<NB, 1>(p, y_t, s);
-  if (pl <= 2) return launch_fp<NB, 2>(p, y_t, s);
-  if (pl <= 4) return launch_fp<NB, 4>(p, y_t, s);
-  if (pl <= 8) return launch_fp<NB, 8>(p, y_t, s);
-  return launch_fp<NB, 0>(p, y_t, s);
+  const int32_t pl = (groups * p.K + 3) / 4;
+  if (pl <= 1) return launch_fp<NB, 1, true>(p, y_t, s);
+  if (pl <= 2) return launch_fp<NB, 2, true>(p, y_t, s);
+  if (pl <= 4) return launch_fp<NB, 4, true>(p, y_t, s);
+  return launch_fp<NB, 4, false>(p, y_t, s);
 }
 
 }  // namespace
@@ -316,6 +344,7 @@ hipError_t launch_spmm_bits(const void* X, int64_t N, int64_t C, const void* val
   p.relu = relu;
   if (N <= 16) return launch_f<1>(p, y_t, s);
   if (N <= 32) return launch_f<2>(p, y_t, s);
+  if (N <= 48) return launch_f<3>(p, y_t, s);
   return launch_f<4>(p, y_t, s);
 }
 

@@ -86,3 +86,15 @@ def test_spmm_bits_fc4096_every_output(N, K):
     from paper_1910_11971_amd import workloads
     X, W = workloads.draw(workloads.WORKLOADS[f"fc4096_k{K}"])
     run_bits(N, 4096, 4096, 16, K, X=X[:N].float().numpy(), W=W)
+
+
+@pytest.mark.parametrize("N,C,O,G,K", [
+    # chunk remainders (32, 64, 96 columns), waves without a chunk, several rounds of chunks, 33..48 rows
+    (48, 4192, 32, 16, 4), (37, 1120, 20, 4, 2), (1, 4576, 16, 16, 1), (33, 2112, 64, 16, 16), (16, 8256, 16, 8, 8),
+    # every index width of the units: 1, 3, 5, 6, 7 bits; packed rows beyond one pass
+    (7, 416, 32, 2, 1), (20, 352, 40, 5, 3), (3, 160, 64, 32, 3), (5, 288, 64, 64, 40), (40, 224, 128, 128, 70),
+    (12, 192, 36, 9, 4),
+])
+def test_spmm_bits_chunks(N, C, O, G, K):
+    need_gpu()
+    run_bits(N, C, O, G, K, seed=N + C + G, ep=True)
