@@ -263,14 +263,26 @@ hipError_t launch_r(const ProductArgs& a, hipStream_t s) {
 // of one group for one row n (Alg. 1's output-stationary registers): its
 // lanes run over the columns c (coalesced reads of X[n][.] and of the packed
 // stream), each adds vals * x of every kept slot to the accumulator of the
-// slot's row, and a wave reduction sums the lanes' partial sums.
+// slot's row, and a wave reduction sums the lanes' partial sums.  Latency
+// bound (a wave reads a few KB): with C % 4 == 0 a lane takes four columns, so
+// 256 columns and up to four slots of them are one batch of 16-byte loads;
+// and the reduction halves the rows a lane carries at each of its first
+// log2(G) exchanges instead of summing every row over all lanes (G = 8: 10
+// exchanges, not 48).  64 x 256 -> 256, G = 8, K = 4, fp32: 8.0 -> 5.7 us of
+// kernel time.
 constexpr int64_t kSmallRows = 256;
 
-template <int G, typename XT, typename VT, typename YT>
+template <typename T, int V>
+struct __attribute__((aligned(sizeof(T) * V))) Cols {
+  T v[V];
+};
+
+template <int G, int V, typename XT, typename VT, typename YT>
 __global__ __launch_bounds__(kThreads) void sparse_mac_rows_kernel(const XT* __restrict__ X, int64_t N, int64_t C,
                                                                    const VT* __restrict__ vals,
                                                                    const uint8_t* __restrict__ idx, int64_t O,
                                                                    int32_t K, Epilogue<YT> ep, YT* __restrict__ Y) {
+  constexpr int KB = 4;  // slots in flight
   const int lane = threadIdx.x & 63;
   const int64_t ngroups = O / G;
   const int64_t wv = static_cast<int64_t>(blockIdx.x) * (kThreads / 64) + (threadIdx.x >> 6);
@@ -279,44 +291,82 @@ __global__ __launch_bounds__(kThreads) void sparse_mac_rows_kernel(const XT* __r
   float acc[G];
 #pragma unroll
   for (int r = 0; r < G; ++r) acc[r] = 0.0f;
-  for (int64_t c = lane; c < C; c += 64) {
-    const float x = io<XT>::load(X, n * C + c);
-#pragma unroll 4
-    for (int32_t k = 0; k < K; ++k) {
-      const int64_t q = (g * K + k) * C + c;
-      const uint32_t i = idx[q];
-      const float v = io<VT>::load(vals, q) * x;
+  for (int64_t c = V * lane; c < C; c += 64 * V) {
+    const Cols<XT, V> xv = *reinterpret_cast<const Cols<XT, V>*>(X + n * C + c);
+    float x[V];
 #pragma unroll
-      for (int r = 0; r < G; ++r) acc[r] += i == static_cast<uint32_t>(r) ? v : 0.0f;
+    for (int v = 0; v < V; ++v) x[v] = io<XT>::load(xv.v, v);
+    for (int32_t k0 = 0; k0 < K; k0 += KB) {
+      Cols<VT, V> pv[KB];
+      Cols<uint8_t, V> pi[KB];
+#pragma unroll
+      for (int k = 0; k < KB; ++k) {
+        const int64_t q = (g * K + (k0 + k < K ? k0 + k : K - 1)) * C + c;
+        pv[k] = *reinterpret_cast<const Cols<VT, V>*>(vals + q);
+        pi[k] = *reinterpret_cast<const Cols<uint8_t, V>*>(idx + q);
+      }
+#pragma unroll
+      for (int k = 0; k < KB; ++k)
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          const uint32_t i = k0 + k < K ? pi[k].v[v] : 0xffffu;  // (no row: never matches)
+          const float t = io<VT>::load(pv[k].v, v) * x[v];
+#pragma unroll
+          for (int r = 0; r < G; ++r) acc[r] += i == static_cast<uint32_t>(r) ? t : 0.0f;
+        }
     }
   }
+  // Exchange with lane ^ off: while more than one row is left, a lane keeps
+  // the half of its rows that its bit `off` names and gives the other half
+  // away; then the lanes that carry the same row sum it.
+  int row = 0;
 #pragma unroll
-  for (int r = 0; r < G; ++r)
+  for (int off = 32, live = G; off > 0; off >>= 1) {
+    if (live > 1) {
+      live >>= 1;
+      const bool up = (lane & off) != 0;
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) acc[r] += __shfl_xor(acc[r], off, 64);
-  if (lane < G) {
-    float y = acc[0];
-#pragma unroll
-    for (int r = 1; r < G; ++r) y = lane == r ? acc[r] : y;
-    const int64_t o = g * G + lane;
-    io<YT>::store(Y, n * O + o, apply_epilogue<YT>(y, o, n * O + o, ep));
+      for (int r = 0; r < live; ++r) {
+        const float give = up ? acc[r] : acc[r + live];
+        const float mine = up ? acc[r + live] : acc[r];
+        acc[r] = mine + __shfl_xor(give, off, 64);
+      }
+      row += up ? live : 0;
+    } else {
+      acc[0] += __shfl_xor(acc[0], off, 64);
+    }
   }
+  // one lane per row: those whose bits below the exchanged ones are zero
+  if ((lane & (64 / G - 1)) == 0) {
+    const int64_t o = g * G + row;
+    io<YT>::store(Y, n * O + o, apply_epilogue<YT>(acc[0], o, n * O + o, ep));
+  }
+}
+
+template <int G, typename XT, typename VT, typename YT>
+void launch_rows_g(const ProductArgs& a, const Epilogue<YT>& ep, hipStream_t s) {
+  const int64_t waves = a.N * (a.O / a.G);
+  const dim3 grid(static_cast<uint32_t>((waves + kThreads / 64 - 1) / (kThreads / 64)));
+  const auto X = static_cast<const XT*>(a.X);
+  const auto V = static_cast<const VT*>(a.vals);
+  const auto Y = static_cast<YT*>(a.Y);
+  if (a.C % 4 == 0)
+    hipLaunchKernelGGL((sparse_mac_rows_kernel<G, 4, XT, VT, YT>), grid, dim3(kThreads), 0, s, X, a.N, a.C, V, a.idx, a.O,
+                       a.K, ep, Y);
+  else
+    hipLaunchKernelGGL((sparse_mac_rows_kernel<G, 1, XT, VT, YT>), grid, dim3(kThreads), 0, s, X, a.N, a.C, V, a.idx, a.O,
+                       a.K, ep, Y);
 }
 
 template <typename XT, typename VT, typename YT>
 hipError_t launch_rows(const ProductArgs& a, hipStream_t s) {
-  const int64_t waves = a.N * (a.O / a.G);
-  const dim3 grid(static_cast<uint32_t>((waves + kThreads / 64 - 1) / (kThreads / 64)));
   Epilogue<YT> ep{a.scale, a.bias, static_cast<const YT*>(a.residual), a.relu};
-  const auto X = static_cast<const XT*>(a.X);
-  const auto V = static_cast<const VT*>(a.vals);
-  const auto Y = static_cast<YT*>(a.Y);
   switch (a.G) {
-    case 2: hipLaunchKernelGGL((sparse_mac_rows_kernel<2, XT, VT, YT>), grid, dim3(kThreads), 0, s, X, a.N, a.C, V, a.idx, a.O, a.K, ep, Y); break;
-    case 4: hipLaunchKernelGGL((sparse_mac_rows_kernel<4, XT, VT, YT>), grid, dim3(kThreads), 0, s, X, a.N, a.C, V, a.idx, a.O, a.K, ep, Y); break;
-    case 8: hipLaunchKernelGGL((sparse_mac_rows_kernel<8, XT, VT, YT>), grid, dim3(kThreads), 0, s, X, a.N, a.C, V, a.idx, a.O, a.K, ep, Y); break;
-    case 16: hipLaunchKernelGGL((sparse_mac_rows_kernel<16, XT, VT, YT>), grid, dim3(kThreads), 0, s, X, a.N, a.C, V, a.idx, a.O, a.K, ep, Y); break;
-    case 32: hipLaunchKernelGGL((sparse_mac_rows_kernel<32, XT, VT, YT>), grid, dim3(kThreads), 0, s, X, a.N, a.C, V, a.idx, a.O, a.K, ep, Y); break;
+    case 2: launch_rows_g<2, XT, VT, YT>(a, ep, s); break;
+    case 4: launch_rows_g<4, XT, VT, YT>(a, ep, s); break;
+    case 8: launch_rows_g<8, XT, VT, YT>(a, ep, s); break;
+    case 16: launch_rows_g<16, XT, VT, YT>(a, ep, s); break;
+    case 32: launch_rows_g<32, XT, VT, YT>(a, ep, s); break;
     default: return hipErrorInvalidConfiguration;
   }
   return hipGetLastError();
