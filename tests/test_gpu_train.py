@@ -144,3 +144,15 @@ def test_training_step_at_the_end_of_the_ramp():
     rows = (np.arange(O // G)[:, None, None] * G + ix).astype(np.int64)
     terms = (np.abs(d.astype(np.float64)).T @ np.abs(x.astype(np.float64)))[rows, np.arange(C)[None, None, :]]
     check_close(to_np_f32(dv), oracle.grad_packed(d, x, ix, G), terms, TOL["bf16"], "dvals")
+
+
+@pytest.mark.parametrize("G", [2, 4, 8, 16, 32])
+def test_td_mask_ties_every_candidate_count(G):
+    """Few distinct magnitudes (zeros, signed zeros, infinities among them): the rows equal to the edge are told apart
+    by their order, for every number of candidates."""
+    need_gpu()
+    rng = np.random.default_rng(G)
+    O, C = 2 * G, 70
+    W = rng.choice(np.array([0.0, -0.0, 1.0, -1.0, 2.0, np.inf, -np.inf], np.float32), (O, C))
+    for n_t in range(G + 1):
+        run_mask(W, G, n_t, rand_bits((O, C), n_t), 0.5, torch.bfloat16)
