@@ -106,16 +106,23 @@ def _check(status: int):
         raise CCIError(status, _lib.cci_last_error().decode() or _lib.cci_status_str(status).decode())
 
 
+# The small products run for 5-10 us, about as long as the marshalling of
+# one call took (8 us), so it is kept short: pointers go to ctypes as plain
+# integers (argtypes convert them), the stream as torch's raw handle, and an
+# epilogue without any term as NULL.
+_CODES = {torch.float32: F32, torch.bfloat16: BF16}
+_raw_stream = torch._C._cuda_getCurrentRawStream
+
+
 def _code(dt: torch.dtype) -> int:
-    if dt == torch.float32:
-        return F32
-    if dt == torch.bfloat16:
-        return BF16
-    raise TypeError(f"unsupported dtype {dt}")
+    try:
+        return _CODES[dt]
+    except KeyError:
+        raise TypeError(f"unsupported dtype {dt}") from None
 
 
 def _ptr(t: torch.Tensor | None):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _dev(t: torch.Tensor) -> torch.Tensor:
@@ -127,7 +134,7 @@ def _dev(t: torch.Tensor) -> torch.Tensor:
 
 
 def _stream(t: torch.Tensor):
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+    return _raw_stream(t.get_device())
 
 
 def _algo(algo) -> int:
@@ -172,7 +179,9 @@ def pack(W: torch.Tensor, G: int, K: int, val_dtype=torch.bfloat16, out=None):
 def _epilogue(scale, bias, residual, relu, O, y_shape, y_dtype, device):
     """Marshal the fused epilogue after checking what the kernels will read:
     scale / bias fp32 [O], residual of Y's shape and dtype, all contiguous
-    on Y's device."""
+    on Y's device.  None (a null pointer) when there is no term."""
+    if scale is None and bias is None and residual is None and not relu:
+        return None
     for name, t in (("scale", scale), ("bias", bias)):
         if t is not None:
             _dev(t)
@@ -180,9 +189,9 @@ def _epilogue(scale, bias, residual, relu, O, y_shape, y_dtype, device):
                 raise ValueError(f"{name} must be a contiguous float32 tensor of {O} elements on {device}")
     if residual is not None:
         _dev(residual)
-        if tuple(residual.shape) != tuple(y_shape) or residual.dtype != y_dtype or residual.device != device:
+        if residual.shape != y_shape or residual.dtype != y_dtype or residual.device != device:
             raise ValueError(f"residual must be a contiguous {y_dtype} tensor of shape {tuple(y_shape)} on {device}")
-    return Epilogue(_ptr(scale), _ptr(bias), _ptr(residual), int(bool(relu)))
+    return ctypes.byref(Epilogue(_ptr(scale), _ptr(bias), _ptr(residual), 1 if relu else 0))
 
 
 def _out(out, shape, dtype, device):
@@ -203,12 +212,13 @@ def spmm(X: torch.Tensor, vals: torch.Tensor, idx: torch.Tensor, G: int, *, scal
     ng, K, C2 = vals.shape
     if C2 != C or tuple(idx.shape) != tuple(vals.shape) or idx.dtype != torch.uint8:
         raise ValueError("shape mismatch between X and packed weights")
-    if vals.device != X.device or idx.device != X.device:
+    dev = X.device
+    if vals.device != dev or idx.device != dev:
         raise ValueError("X and the packed weights must be on one device")
     O = ng * G
     Y = _out(out, (N, O), out_dtype or X.dtype, X.device)
     ep = _epilogue(scale, bias, residual, relu, O, Y.shape, Y.dtype, X.device)
-    args = (_ptr(X), _code(X.dtype), N, C, _ptr(vals), _code(vals.dtype), _ptr(idx), O, G, K, ctypes.byref(ep),
+    args = (_ptr(X), _code(X.dtype), N, C, _ptr(vals), _code(vals.dtype), _ptr(idx), O, G, K, ep,
             _ptr(Y), _code(Y.dtype))
     a = _algo(algo)
     _check(_lib.cci_spmm(*args, _stream(X)) if a == ALGO_AUTO else _lib.cci_spmm_algo(*args, a, _stream(X)))
@@ -229,14 +239,15 @@ def conv_im2col(X: torch.Tensor, vals: torch.Tensor, idx: torch.Tensor, G: int, 
     ng, K, C = vals.shape
     if C != KH * KW * Cin or tuple(idx.shape) != tuple(vals.shape) or idx.dtype != torch.uint8:
         raise ValueError("packed weights do not match KH*KW*Cin")
-    if vals.device != X.device or idx.device != X.device:
+    dev = X.device
+    if vals.device != dev or idx.device != dev:
         raise ValueError("X and the packed weights must be on one device")
     O = ng * G
     Ho, Wo = conv_out_hw(H, W, KH, KW, stride, pad)
     Y = _out(out, (B, Ho, Wo, O), out_dtype or X.dtype, X.device)
     ep = _epilogue(scale, bias, residual, relu, O, Y.shape, Y.dtype, X.device)
     args = (_ptr(X), _code(X.dtype), B, H, W, Cin, KH, KW, stride[0], stride[1], pad[0], pad[1], _ptr(vals),
-            _code(vals.dtype), _ptr(idx), O, G, K, ctypes.byref(ep), _ptr(Y), _code(Y.dtype))
+            _code(vals.dtype), _ptr(idx), O, G, K, ep, _ptr(Y), _code(Y.dtype))
     a = _algo(algo)
     _check(_lib.cci_conv_im2col(*args, _stream(X)) if a == ALGO_AUTO
            else _lib.cci_conv_im2col_algo(*args, a, _stream(X)))
@@ -332,7 +343,7 @@ def spmm_2of4(X: torch.Tensor, a_vals: torch.Tensor, a_idx: torch.Tensor, *, sca
         raise ValueError("X and the operand must be on one device")
     Y = _out(out, (N, M), out_dtype or X.dtype, X.device)
     ep = _epilogue(scale, bias, residual, relu, M, Y.shape, Y.dtype, X.device)
-    _check(_lib.cci_spmm_2of4(_ptr(X), _code(X.dtype), N, R, _ptr(a_vals), _ptr(a_idx), M, ctypes.byref(ep), _ptr(Y),
+    _check(_lib.cci_spmm_2of4(_ptr(X), _code(X.dtype), N, R, _ptr(a_vals), _ptr(a_idx), M, ep, _ptr(Y),
                               _code(Y.dtype), _stream(X)))
     return Y
 
@@ -414,5 +425,5 @@ def spmm_bits(X: torch.Tensor, vals: torch.Tensor, idx: torch.Tensor, G: int, id
     Y = _out(out, (N, O), out_dtype or X.dtype, X.device)
     ep = _epilogue(scale, bias, residual, relu, O, Y.shape, Y.dtype, X.device)
     _check(_lib.cci_spmm_bits(_ptr(X), _code(X.dtype), N, C, _ptr(vals), _code(vals.dtype), _ptr(idx), idx_bits, O, G,
-                              K, ctypes.byref(ep), _ptr(Y), _code(Y.dtype), _stream(X)))
+                              K, ep, _ptr(Y), _code(Y.dtype), _stream(X)))
     return Y

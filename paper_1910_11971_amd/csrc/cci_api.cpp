@@ -84,10 +84,17 @@ bool few_rows_ok(const cci::ProductArgs& a) {
 // split-reduction kernels take the ones of few tiles, and they and the
 // tap-chunk kernels also run reductions in blocks of 8 (one tap) and a
 // ragged last output tile.
-cci_algo ragged_route(const cci::ProductArgs& a, cci_algo chosen) {
-  if (chosen != CCI_ALGO_NARROW_MFMA && chosen != CCI_ALGO_DENSE_TILE_MFMA && chosen != CCI_ALGO_SPARSE_MAC &&
-      chosen != CCI_ALGO_TAP_TILE_MFMA)
-    return chosen;
+// (mac_next: the dense-tile kernels, where they refuse, are followed by the
+// sparse-MAC ones.)  A product that the family it is taken from refuses keeps
+// being refused.
+cci_algo ragged_route(cci::ProductArgs& a, cci_algo chosen, bool mac_next) {
+  a.ragged = true;
+  const auto accepted = [&] {
+    if (chosen == CCI_ALGO_SPARSE_MAC) return cci::sparse_mac_supports(a);
+    if (chosen == CCI_ALGO_DENSE_TILE_MFMA)
+      return (mac_next && cci::sparse_mac_supports(a)) || cci::dense_tile_supports(a);
+    return chosen == CCI_ALGO_NARROW_MFMA || chosen == CCI_ALGO_TAP_TILE_MFMA;
+  };
   // Few 64 x 32 tiles: the split-reduction kernels (us, split / best other:
   // 49 x 1344 -> 224 7.0 / 14.0; 196 x 816 -> 136 5.2 / 11.1; 196 x 136 ->
   // 816 4.8 / 6.8; 784 x 512 -> 128 5.2 / 8.0; 392 x 2048 -> 512 11.2 / 18.4;
@@ -95,14 +102,16 @@ cci_algo ragged_route(const cci::ProductArgs& a, cci_algo chosen) {
   // reductions go to the tap-chunk kernels (3136 x 1344 -> 224 17.5 / 15.4;
   // 700 x 1184 -> 624 15.7 / 13.6).
   const int64_t t64x32 = (a.N + 63) / 64 * ((a.O + 31) / 32);
-  if (a.C >= 64 && t64x32 <= (a.C <= 1024 ? 256 : 128) && cci::split_k_takes(a)) return CCI_ALGO_SPLIT_K_MFMA;
+  if (a.C >= 64 && t64x32 <= (a.C <= 1024 ? 256 : 128) && cci::split_k_supports(a) && accepted())
+    return CCI_ALGO_SPLIT_K_MFMA;
   // From 96 columns on the tap-chunk kernels are ahead of the dense-tile ones
   // (us, tap / dense or narrow: 12544 x 576 -> 96 10.6 / 14.7; 12544 x 96 ->
   // 576 11.1 / 17.1; 6272 x 192 -> 1152 12.2 / 21.2; 12544 x 816 -> 136 15.6
   // / 1054 on the sparse-MAC kernels; a 3x3 stride-2 convolution 64 -> 64 over
   // 200 704 output pixels 52.8 / 80.7), except where the narrow ones stream
   // >= 100 K rows (200704 x 192 -> 32 28.6 / 24.0).
-  if (a.C >= 96 && !(chosen == CCI_ALGO_NARROW_MFMA && a.N >= 100000) && cci::tap_tile_takes(a))
+  if (a.C >= 96 && chosen != CCI_ALGO_TAP_TILE_MFMA && !(chosen == CCI_ALGO_NARROW_MFMA && a.N >= 100000) &&
+      cci::tap_tile_supports(a) && accepted())
     return CCI_ALGO_TAP_TILE_MFMA;
   return chosen;
 }
@@ -123,38 +132,41 @@ cci_status run_product(cci::ProductArgs& a, cci_algo algo, const cci_epilogue* e
     return fail(CCI_EINVAL, "unknown algo %d", (int)algo);
   if (a.N == 0) return ok();
 
-  const bool mac_ok = cci::sparse_mac_supports(a);
-  const bool tile_ok = cci::dense_tile_supports(a);
   cci_algo chosen = algo;
+  bool mac_next = false;  // AUTO: a product the dense-tile kernels refuse goes to the sparse-MAC ones
   if (algo == CCI_ALGO_AUTO) {
     const int64_t cin = a.conv ? a.geom.Cin : a.C;
     chosen = cci_auto_algo(a.x_t == cci::DType::F32 ? CCI_F32 : CCI_BF16,
                            a.val_t == cci::DType::F32 ? CCI_F32 : CCI_BF16, a.N, a.C, cin, a.O,
                            a.G, a.K);
+    // (the shape-only choice cannot see stride, padding and alignment)
+    bool ok = true;
+    switch (chosen) {
+      case CCI_ALGO_FEW_ROWS_MFMA: ok = few_rows_ok(a); break;
+      case CCI_ALGO_RESIDENT_MFMA: ok = cci::resident_supports(a); break;
+      case CCI_ALGO_WIDE_TILE_MFMA: ok = cci::wide_tile_supports(a); break;
+      case CCI_ALGO_NARROW_MFMA: ok = cci::narrow_supports(a); break;
+      case CCI_ALGO_TAP_TILE_MFMA: ok = cci::tap_tile_supports(a); break;
+      case CCI_ALGO_STREAM_TILE_MFMA: ok = cci::stream_tile_supports(a); break;
+      case CCI_ALGO_SPLIT_K_MFMA: ok = cci::split_k_supports(a); break;
+      default: break;
+    }
+    if (!ok) {
+      const bool tap = (chosen == CCI_ALGO_WIDE_TILE_MFMA || chosen == CCI_ALGO_STREAM_TILE_MFMA) &&
+                       cci::tap_tile_supports(a);
+      mac_next = !tap && chosen != CCI_ALGO_WIDE_TILE_MFMA;
+      chosen = tap ? CCI_ALGO_TAP_TILE_MFMA : CCI_ALGO_DENSE_TILE_MFMA;
+    }
   }
-  // (the shape-only choice cannot see stride and padding)
-  if (algo == CCI_ALGO_AUTO && chosen == CCI_ALGO_FEW_ROWS_MFMA && !few_rows_ok(a))
-    chosen = tile_ok ? CCI_ALGO_DENSE_TILE_MFMA : CCI_ALGO_SPARSE_MAC;
-  if (algo == CCI_ALGO_AUTO && chosen == CCI_ALGO_RESIDENT_MFMA && !cci::resident_supports(a))
-    chosen = tile_ok ? CCI_ALGO_DENSE_TILE_MFMA : CCI_ALGO_SPARSE_MAC;
-  if (algo == CCI_ALGO_AUTO && chosen == CCI_ALGO_WIDE_TILE_MFMA && !cci::wide_tile_supports(a))
-    chosen = cci::tap_tile_supports(a) ? CCI_ALGO_TAP_TILE_MFMA : CCI_ALGO_DENSE_TILE_MFMA;
-  if (algo == CCI_ALGO_AUTO && chosen == CCI_ALGO_NARROW_MFMA && !cci::narrow_supports(a))
-    chosen = tile_ok ? CCI_ALGO_DENSE_TILE_MFMA : CCI_ALGO_SPARSE_MAC;
-  if (algo == CCI_ALGO_AUTO && chosen == CCI_ALGO_TAP_TILE_MFMA && !cci::tap_tile_supports(a))
-    chosen = tile_ok ? CCI_ALGO_DENSE_TILE_MFMA : CCI_ALGO_SPARSE_MAC;
-  if (algo == CCI_ALGO_AUTO && chosen == CCI_ALGO_STREAM_TILE_MFMA && !cci::stream_tile_supports(a))
-    chosen = cci::tap_tile_supports(a) ? CCI_ALGO_TAP_TILE_MFMA : tile_ok ? CCI_ALGO_DENSE_TILE_MFMA : CCI_ALGO_SPARSE_MAC;
-  if (algo == CCI_ALGO_AUTO && chosen == CCI_ALGO_SPLIT_K_MFMA && !cci::split_k_supports(a))
-    chosen = tile_ok ? CCI_ALGO_DENSE_TILE_MFMA : CCI_ALGO_SPARSE_MAC;
-  if (algo == CCI_ALGO_AUTO) chosen = ragged_route(a, chosen);
-  // (a pinned family takes its whole tiles only; AUTO also its ragged forms)
-  const bool pinned = algo != CCI_ALGO_AUTO;
-  if (chosen == CCI_ALGO_SPARSE_MAC && !mac_ok)
+  if (algo == CCI_ALGO_AUTO) chosen = ragged_route(a, chosen, mac_next);
+  if (chosen == CCI_ALGO_DENSE_TILE_MFMA && !cci::dense_tile_supports(a)) {
+    if (!mac_next)
+      return fail(CCI_EUNSUPPORTED,
+                  "dense-tile MFMA kernels need bf16 X/vals, 64 %% G == 0 and C (conv: Cin) %% 32 == 0");
+    chosen = CCI_ALGO_SPARSE_MAC;
+  }
+  if (chosen == CCI_ALGO_SPARSE_MAC && !cci::sparse_mac_supports(a))
     return fail(CCI_EUNSUPPORTED, "sparse-MAC kernels need G in {2,4,8,16,32} (G=%d)", a.G);
-  if (chosen == CCI_ALGO_DENSE_TILE_MFMA && !tile_ok)
-    return fail(CCI_EUNSUPPORTED,
-                "dense-tile MFMA kernels need bf16 X/vals, 64 %% G == 0 and C (conv: Cin) %% 32 == 0");
   if (chosen == CCI_ALGO_WIDE_TILE_MFMA && !cci::wide_tile_supports(a))
     return fail(CCI_EUNSUPPORTED,
                 "wide-tile MFMA kernels need bf16 X/vals, an FC or stride-1 unpadded 1x1 product, "
@@ -172,7 +184,7 @@ cci_status run_product(cci::ProductArgs& a, cci_algo algo, const cci_epilogue* e
                 "narrow MFMA kernels need bf16 X/vals, C <= 256, C %% 8 == 0, O %% 4 == 0, G <= 256, "
                 "aligned pointers, and for a conv other than 1x1 stride 1 unpadded Cin %% 8 == 0 or "
                 "Cin == 4 with an even KW");
-  if (chosen == CCI_ALGO_TAP_TILE_MFMA && pinned && !cci::tap_tile_supports(a))
+  if (chosen == CCI_ALGO_TAP_TILE_MFMA && !cci::tap_tile_supports(a))
     return fail(CCI_EUNSUPPORTED,
                 "tap-tile MFMA kernels need bf16 X/vals, Cin (FC: C) %% 64 == 0, O %% 128 == 0 with 32 %% G == 0 "
                 "or O %% 64 == 0 with 16 %% G == 0, 2 K <= G or K == G, at most 32 filter taps and aligned "
@@ -181,7 +193,7 @@ cci_status run_product(cci::ProductArgs& a, cci_algo algo, const cci_epilogue* e
     return fail(CCI_EUNSUPPORTED,
                 "stream-tile MFMA kernels need bf16 X/vals, an FC or stride-1 unpadded 1x1 product, "
                 "C %% 64 == 0 with C <= 256, O %% 64 == 0, 32 %% G == 0 and aligned pointers");
-  if (chosen == CCI_ALGO_SPLIT_K_MFMA && pinned && !cci::split_k_supports(a))
+  if (chosen == CCI_ALGO_SPLIT_K_MFMA && !cci::split_k_supports(a))
     return fail(CCI_EUNSUPPORTED,
                 "split-K MFMA kernels need bf16 X/vals, an FC or stride-1 unpadded 1x1 product, "
                 "C %% 32 == 0, O %% 16 == 0, K <= 4 and 16-byte aligned pointers");

@@ -887,14 +887,28 @@ bool layout(Params& pl, int32_t cinb, int32_t Cin, int32_t wres, int32_t npb, in
 constexpr double kPatchBpc = 20.0;      // patch / output bytes per cycle per CU
 constexpr double kUnitCycles = 400.0;   // one expansion unit (packed row segment) per expander lane
 constexpr double kMfmaCycles = 20.0;    // one 16x16x32 MFMA with its operand reads
+constexpr double kLatency = 5633.0, kBarrier = 100.0, kSetup = 1813.0;
+// (kChunkLatency: ResNet-50's 3x3 layers' chunks were measured at 6.5-10 K
+// cycles almost independently of the part's pixel count)
+constexpr double kChunkLatency = 1873.0;
+
+// No plan of n chunks is modelled faster than this, whatever its layout: the
+// first chunk's arrival, then either every chunk's MFMAs or every further
+// chunk's arrival (after the previous one's MFMAs with one patch buffer).
+double least_cycles(int n, double load, double mfma_chunk, double store, int npb) {
+  const double first = kSetup / 2 + kLatency + load;
+  const double start = first > kSetup + kLatency ? first : kSetup + kLatency;
+  const double mfma = start + n * mfma_chunk + (n - 1) * (kBarrier + (npb == 1 ? kChunkLatency + load : 0.0));
+  const double stream = first + (n - 1) * (kChunkLatency + load) + mfma_chunk;
+  return (mfma > stream ? mfma : stream) + store;
+}
+
 double model_cycles(const Params& t, double mfma_chunk, double store, int K) {
   const double load = t.patch_pix * static_cast<double>(t.cinb) * 2.0 / kPatchBpc;
   // expansion by the 256 expander threads: zero fill (b128 writes) and
   // K packed-row segments per unit
   const double build = t.w_bytes / 16.0 / kRoleThreads * 8.0 + t.nu * K * kUnitCycles;
-  // (chunk_latency: ResNet-50's 3x3 layers' chunks were measured at 6.5-10 K
-  // cycles almost independently of the part's pixel count)
-  const double latency = 5633.0, barrier = 100.0, setup = 1813.0, chunk_latency = 1873.0;
+  const double latency = kLatency, barrier = kBarrier, setup = kSetup, chunk_latency = kChunkLatency;
   const double e_first = setup + latency + build * (t.wres ? 1 : 2);
   double arrive = setup / 2 + latency + load, done = 0.0, start = 0.0;
   double done2 = 0.0;  // done time of chunk c-2
@@ -923,7 +937,8 @@ double model_cycles(const Params& t, double mfma_chunk, double store, int K) {
 // Choose the wave arrangement, pixel partition, channel chunk and LDS plan
 // with the smallest modelled time on the busiest CU (one workgroup per CU at
 // a time).
-bool make_plan(const ProductArgs& a, Params& best, uint32_t& grid) {
+// any: stop at the first plan that fits.
+bool make_plan(const ProductArgs& a, Params& best, uint32_t& grid, bool any = false) {
   const int32_t Cin = a.conv ? a.geom.Cin : static_cast<int32_t>(a.C);
   const bool rows = is_rows_mode(a);
   const int32_t taps = a.conv ? a.geom.KH * a.geom.KW : 1;
@@ -980,8 +995,15 @@ bool make_plan(const ProductArgs& a, Params& best, uint32_t& grid) {
         const double mfma_chunk = static_cast<double>(simd_tiles) * taps * (cinb / kKS) * 4.0 * kMfmaCycles;
         for (int32_t wres = 1; wres >= 0; --wres) {
           for (int32_t npb = 1; npb <= 2; ++npb) {
+            // (most candidates end here: laying every one out and modelling it
+            // chunk by chunk took 50-150 us of host time a call, more than
+            // most of these products run)
+            const double load = pl.patch_pix * static_cast<double>(cinb) * 2.0 / kPatchBpc;
+            if (0.999 * static_cast<double>(per_cu) * least_cycles(Cin / cinb, load, mfma_chunk, store, npb) >= best_cost)
+              continue;
             Params t = pl;
             if (!layout(t, cinb, Cin, wres, npb, a.G, a.K)) continue;
+            if (any) return true;
             const double cost = static_cast<double>(per_cu) * model_cycles(t, mfma_chunk, store, a.K);
             if (cost < best_cost) {
               best_cost = cost;
@@ -1089,7 +1111,7 @@ bool dense_tile_supports(const ProductArgs& a) {
   if (x_elems * 2 >= lim / 2 || y_bytes >= lim || p_bytes >= lim) return false;
   Params pl;
   uint32_t grid;
-  return make_plan(a, pl, grid);
+  return make_plan(a, pl, grid, true);
 }
 
 hipError_t launch_dense_tile(const ProductArgs& a, hipStream_t s) {

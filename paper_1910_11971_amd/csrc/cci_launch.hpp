@@ -55,6 +55,7 @@ struct ProductArgs {
   int32_t relu;
   void* Y;
   DType y_t;
+  bool ragged = false;   // AUTO: the tap-chunk and split-reduction families' ragged forms too
 };
 
 hipError_t launch_pack(const float* W, int64_t O, int64_t C, int32_t G, int32_t K,
@@ -65,6 +66,8 @@ bool sparse_mac_supports(const ProductArgs& a);
 hipError_t launch_sparse_mac(const ProductArgs& a, hipStream_t s);
 
 // Packed groups expanded to dense bf16 tiles in LDS, bf16 MFMA.
+// dense_tile_supports: within its limits, and some plan fits (found without
+// modelling any).
 bool dense_tile_supports(const ProductArgs& a);
 hipError_t launch_dense_tile(const ProductArgs& a, hipStream_t s);
 
@@ -92,10 +95,9 @@ hipError_t launch_resident(const ProductArgs& a, hipStream_t s);
 // reduction splits into chunks of 64 channels under one tap (Cin % 64 == 0):
 // 128 x 128 workgroup tiles, two workgroups per CU (bf16; O % 128 == 0,
 // 32 % G == 0, KH * KW <= 32).
-// tap_tile_takes: also O % 8 == 0 (a ragged last output tile) and, for one
-// tap, C % 8 == 0 (a short last chunk); AUTO uses these.
+// With a.ragged also O % 8 == 0 (a ragged last output tile) and, for one
+// tap, C % 8 == 0 (a short last chunk).
 bool tap_tile_supports(const ProductArgs& a);
-bool tap_tile_takes(const ProductArgs& a);
 hipError_t launch_tap_tile(const ProductArgs& a, hipStream_t s);
 
 // FC products and stride-1 1x1 convolutions with 64 <= C <= 256: a workgroup
@@ -109,9 +111,8 @@ hipError_t launch_stream_tile(const ProductArgs& a, hipStream_t s);
 // reduction of one 16 RF x 16 OF tile, each building its weight fragments in
 // registers from the packed entries (bf16 X/vals; FC or stride-1 unpadded
 // 1x1; C % 32 == 0, O % 16 == 0, K <= 4).
-// split_k_takes: also C % 8 == 0 and O % 8 == 0; AUTO uses these.
+// With a.ragged also C % 8 == 0 and O % 8 == 0.
 bool split_k_supports(const ProductArgs& a);
-bool split_k_takes(const ProductArgs& a);
 hipError_t launch_split_k(const ProductArgs& a, hipStream_t s);
 
 // Balanced sparsity (groups of G inputs in one output row) and the 2:4

@@ -430,7 +430,7 @@ static void split_k_tile(int64_t N, int64_t C, int64_t O, int32_t G, int32_t K, 
   }
 }
 
-bool split_k_takes(const ProductArgs& a) {
+bool split_k_supports(const ProductArgs& a) {
   if (a.x_t != DType::BF16 || a.val_t != DType::BF16) return false;
   if (a.G < 1 || a.G > 256 || a.K < 1 || a.K > 4 || a.K > a.G) return false;
   if (a.conv) {
@@ -438,6 +438,7 @@ bool split_k_takes(const ProductArgs& a) {
     if (g.KH != 1 || g.KW != 1 || g.sh != 1 || g.sw != 1 || g.ph != 0 || g.pw != 0) return false;
   }
   if (a.N < 1 || a.C < 32 || a.C % 8 != 0 || a.O % 8 != 0) return false;
+  if (!a.ragged && (a.C % 32 != 0 || a.O % 16 != 0)) return false;
   const auto al = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
   if (!al(a.X) || !al(a.vals) || !al(a.idx) || !al(a.Y) || (a.residual && !al(a.residual))) return false;
   if ((a.scale && !al(a.scale)) || (a.bias && !al(a.bias))) return false;
@@ -446,10 +447,8 @@ bool split_k_takes(const ProductArgs& a) {
   return true;
 }
 
-bool split_k_supports(const ProductArgs& a) { return a.C % 32 == 0 && a.O % 16 == 0 && split_k_takes(a); }
-
 hipError_t launch_split_k(const ProductArgs& a, hipStream_t s) {
-  if (!split_k_takes(a)) return hipErrorInvalidConfiguration;
+  if (!split_k_supports(a)) return hipErrorInvalidConfiguration;
   int32_t rf, of;
   split_k_tile(a.N, a.C, a.O, a.G, a.K, rf, of);
   KParams p{};

@@ -672,7 +672,7 @@ hipError_t launch_ty(const TParams& p, hipStream_t s, int to) {
 
 }  // namespace
 
-bool tap_tile_takes(const ProductArgs& a) {
+bool tap_tile_supports(const ProductArgs& a) {
   if (a.x_t != DType::BF16 || a.val_t != DType::BF16) return false;
   if (a.G < 1 || a.G > 32 || 32 % a.G != 0 || a.K < 1 || a.K > a.G) return false;
   // at most half of each group kept, or all of it (dense control): above
@@ -685,6 +685,7 @@ bool tap_tile_takes(const ProductArgs& a) {
   // reduction may be short (in blocks of 8 columns)
   const int64_t cin = a.conv ? a.geom.Cin : a.C;
   if (cin % kCK != 0 && (cin != a.C || cin % 8 != 0)) return false;
+  if (!a.ragged && (cin % kCK != 0 || a.O % 64 != 0)) return false;
   if (a.conv && a.geom.KH * a.geom.KW > kMaxTaps) return false;
   const auto al = [](const void* q, uintptr_t m) { return (reinterpret_cast<uintptr_t>(q) & (m - 1)) == 0; };
   if (!al(a.X, 16) || !al(a.vals, 16) || !al(a.idx, 8) || !al(a.Y, 16)) return false;
@@ -698,13 +699,8 @@ bool tap_tile_takes(const ProductArgs& a) {
   return true;
 }
 
-bool tap_tile_supports(const ProductArgs& a) {
-  const int64_t cin = a.conv ? a.geom.Cin : a.C;
-  return cin % kCK == 0 && a.O % 64 == 0 && tap_tile_takes(a);
-}
-
 hipError_t launch_tap_tile(const ProductArgs& a, hipStream_t s) {
-  if (!tap_tile_takes(a)) return hipErrorInvalidConfiguration;
+  if (!tap_tile_supports(a)) return hipErrorInvalidConfiguration;
   TParams p{};
   p.X = static_cast<const uint16_t*>(a.X);
   p.vals = static_cast<const uint16_t*>(a.vals);

@@ -124,7 +124,7 @@ RAGGED_CASES = [  # N, C, O, G, K: products AUTO gives to the tap-chunk and spli
     (300, 320, 1008, 16, 8), (300, 1480, 1008, 16, 16), (257, 264, 1032, 8, 8), (40, 1040, 2056, 8, 8),
     # split-reduction: 8, 16 and 24 columns in the last k-step, rows of 8-byte index units, 8 outputs in the last tile
     (49, 1352, 232, 8, 2), (130, 72, 40, 8, 1), (65, 88, 24, 4, 2), (300, 1000, 136, 8, 4), (33, 2072, 56, 8, 3),
-    (100, 5000, 48, 16, 4), (70, 1016, 320, 64, 2),
+    (100, 5000, 48, 16, 4), (70, 1016, 320, 32, 2),
 ]
 
 
@@ -355,3 +355,24 @@ def test_spmm_sparse_mac_small_n_wide_groups(N, C, O, G, K, xdt):
     need_gpu()
     ep = rand_epilogue(O, N, xdt, 17, residual=True, relu=True)
     run_case(rand_x(N, C, xdt, N + 3), rand_w(O, C, O + 5), G, K, xdt, "sparse_mac", ep=ep)
+
+
+@pytest.mark.parametrize("N,C,O,G,K", [(100, 1016, 320, 64, 2), (100, 136, 96, 6, 2)])
+def test_spmm_auto_still_refuses(N, C, O, G, K):
+    """A product that no family took whole is not taken in a ragged form either."""
+    need_gpu()
+    from paper_1910_11971_amd import cci
+    if G == 6:
+        C, O = 300, 96  # past the narrow kernels' reduction
+    vals, idx = cci.pack(torch.from_numpy(rand_w(O, C, 2)).to(DEV), G, K, torch.bfloat16)
+    with pytest.raises(cci.CCIError):
+        cci.spmm(rand_x(N, C, torch.bfloat16, 1).to(DEV), vals, idx, G)
+
+
+@pytest.mark.parametrize("N,C,O,G,K", [(3, 260, 32, 16, 5), (9, 64, 64, 32, 31), (2, 1024, 8, 2, 1), (255, 20, 16, 4, 4),
+                                       (7, 259, 40, 8, 3), (1, 8, 64, 32, 2)])
+def test_spmm_fp32_few_rows(N, C, O, G, K):
+    """Vector-ALU kernel of few rows: four columns a lane and one, every row exchange, slot remainders."""
+    need_gpu()
+    ep = rand_epilogue(O, N, torch.float32, N + C, residual=True, relu=True)
+    run_case(rand_x(N, C, torch.float32, N), rand_w(O, C, C), G, K, torch.float32, "auto", ep=ep)
