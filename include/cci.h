@@ -245,7 +245,8 @@ cci_status cci_conv_im2col_algo(const void *X, cci_dtype x_t, int64_t B,
  * CCI_ALGO_TAP_TILE_MFMA or CCI_ALGO_SPARSE_MAC runs on the split-reduction
  * kernels when it has few output tiles, or on the tap-chunk ones when its
  * reduction has 96 or more columns, also in ragged forms that cannot be
- * pinned: reductions in blocks of 8 (one tap) and O % 8 == 0. */
+ * pinned: reductions in blocks of 8 (one tap), O % 8 == 0, and (split-
+ * reduction) convolutions of any geometry. */
 cci_algo cci_auto_algo(cci_dtype x_t, cci_dtype val_t, int64_t N, int64_t C,
                        int64_t cin, int64_t O, int32_t G, int32_t K);
 

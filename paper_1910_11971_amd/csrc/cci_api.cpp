@@ -98,11 +98,14 @@ cci_algo ragged_route(cci::ProductArgs& a, cci_algo chosen, bool mac_next) {
   // Few 64 x 32 tiles: the split-reduction kernels (us, split / best other:
   // 49 x 1344 -> 224 7.0 / 14.0; 196 x 816 -> 136 5.2 / 11.1; 196 x 136 ->
   // 816 4.8 / 6.8; 784 x 512 -> 128 5.2 / 8.0; 392 x 2048 -> 512 11.2 / 18.4;
-  // 300 x 1184 -> 624 10.1 / 13.6).  From half a round of the chip on, longer
-  // reductions go to the tap-chunk kernels (3136 x 1344 -> 224 17.5 / 15.4;
-  // 700 x 1184 -> 624 15.7 / 13.6).
+  // 300 x 1184 -> 624 10.1 / 13.6; a 3x3 layer 256 -> 256 over 196 pixels 10.1
+  // / 21.0).  Its time per tile grows with K (each kept entry of a column is
+  // compared with every row): from half a round of the chip on, longer
+  // reductions with K > 2 go to the tap-chunk kernels (700 x 1184 -> 624, K =
+  // 4, 15.7 / 13.6; 3x3, 256 -> 256 over 1568 pixels, K = 4 22.2 / 21.5, K = 2
+  // 17.8 / 21.1), and beyond a round all do (3136 x 1344 -> 224 17.5 / 15.4).
   const int64_t t64x32 = (a.N + 63) / 64 * ((a.O + 31) / 32);
-  if (a.C >= 64 && t64x32 <= (a.C <= 1024 ? 256 : 128) && cci::split_k_supports(a) && accepted())
+  if (a.C >= 64 && t64x32 <= (a.C <= 1024 || a.K <= 2 ? 256 : 128) && cci::split_k_supports(a) && accepted())
     return CCI_ALGO_SPLIT_K_MFMA;
   // From 96 columns on the tap-chunk kernels are ahead of the dense-tile ones
   // (us, tap / dense or narrow: 12544 x 576 -> 96 10.6 / 14.7; 12544 x 96 ->

@@ -55,7 +55,8 @@ struct ProductArgs {
   int32_t relu;
   void* Y;
   DType y_t;
-  bool ragged = false;   // AUTO: the tap-chunk and split-reduction families' ragged forms too
+  bool ragged = false;   // AUTO: also the forms that the tap-chunk and split-reduction families
+                         // refuse when pinned
 };
 
 hipError_t launch_pack(const float* W, int64_t O, int64_t C, int32_t G, int32_t K,
@@ -111,7 +112,8 @@ hipError_t launch_stream_tile(const ProductArgs& a, hipStream_t s);
 // reduction of one 16 RF x 16 OF tile, each building its weight fragments in
 // registers from the packed entries (bf16 X/vals; FC or stride-1 unpadded
 // 1x1; C % 32 == 0, O % 16 == 0, K <= 4).
-// With a.ragged also C % 8 == 0 and O % 8 == 0.
+// With a.ragged also C % 8 == 0 and O % 8 == 0, and convolutions of any
+// geometry (taps over Cin % 32 == 0).
 bool split_k_supports(const ProductArgs& a);
 hipError_t launch_split_k(const ProductArgs& a, hipStream_t s);
 

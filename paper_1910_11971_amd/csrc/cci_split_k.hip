@@ -26,6 +26,15 @@
 // (a bytewise zero test of idx ^ rr, widened to a 16-bit mask per column)
 // and keeps the matching values.  Distinct kept entries of one column have
 // distinct slots, so at most one value survives per element.
+//
+// Convolutions of any geometry run through implicit im2col (Sec. 3.2) when a
+// k-step lies under one tap (Cin % 32 == 0): each lane keeps, per row, the
+// byte offset of tap (0, 0) and a bit per tap that falls into the padding,
+// and its loads go through the buffer's range check (an offset with bit 31
+// set reads zero).  Small batches of late 3x3 layers leave the tap-chunk
+// kernels a handful of workgroups that walk 9-72 chunks in turn (us, here /
+// tap-chunk: 7x7, 512 -> 512, batch 1 13.4 / 34.6; 14x14, 256 -> 256, batch 1
+// 10.1 / 21.0, batch 8 17.8 / 21.1; 28x28, 128 -> 128, batch 2 9.0 / 13.9).
 #include <type_traits>
 
 #include "cci_device.hpp"
@@ -42,6 +51,9 @@ typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 constexpr int kThreads = 512;  // eight waves
 constexpr int kWaves = 8;
 constexpr int kXcds = 8;
+constexpr int kMaxTaps = 32;              // one validity bit each
+constexpr uint32_t kOOB = 0x80000000u;    // buffer offset that reads as zero
+constexpr int kRsrcWord3 = 0x00020000;    // raw buffer descriptor word 3 (gfx9 family)
 
 struct KParams {
   const uint16_t* X;
@@ -55,6 +67,11 @@ struct KParams {
   int32_t nob;    // output blocks (O / (16 OF), rounded up)
   int32_t tiles;  // row blocks x output blocks
   int32_t tpx;    // tiles per XCD (ceil(tiles / 8))
+  // convolutions read through implicit im2col
+  uint32_t x_bytes;
+  int32_t H, W, Cin, KH, KW, sh, sw, ph, pw, HoWo, Wo;
+  uint32_t spt_mul;  // k-step / (Cin / 32) == mulhi(k-step, spt_mul) (Cin == 32: unused)
+  uint32_t kw_mul;   // tap / KW == (tap * kw_mul) >> 16
 };
 
 // k-steps whose loads a wave keeps in flight together: as many as fit about
@@ -99,7 +116,7 @@ struct Step {
   u32x2_t i[OF][K];
 };
 
-template <int RF, int OF, int K, bool WL, typename YT>
+template <int RF, int OF, int K, bool WL, bool CONV, typename YT>
 __global__ __launch_bounds__(kThreads) void split_k_kernel(KParams p) {
   constexpr int TR = 16 * RF, TO = 16 * OF, PITCH = TO + 4;
   constexpr int U = batch_steps(RF, OF, K, WL);
@@ -114,7 +131,8 @@ __global__ __launch_bounds__(kThreads) void split_k_kernel(KParams p) {
   const int32_t t = (b % kXcds) * p.tpx + b / kXcds;
   if (t >= p.tiles) return;  // whole workgroup: before any barrier
   const int32_t rb = t / p.nob, ob = t - rb * p.nob;
-  const int32_t w = static_cast<int32_t>(threadIdx.x) / 64, lane = static_cast<int32_t>(threadIdx.x) % 64;
+  const int32_t w = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / 64);
+  const int32_t lane = static_cast<int32_t>(threadIdx.x) % 64;
   const int32_t lr = lane % 16, lq = lane / 16;
   const int32_t n0 = rb * TR, o0 = ob * TO;
 
@@ -133,12 +151,32 @@ __global__ __launch_bounds__(kThreads) void split_k_kernel(KParams p) {
     gbase[f] = static_cast<int64_t>(WL ? g - g_lo : g) * K * p.C;
   }
   // X rows past N read row N - 1 (their sums are never stored)
-  const uint16_t* xrow[RF];
+  const uint16_t* xrow[CONV ? 1 : RF];
+  int32_t xoff[CONV ? RF : 1];   // byte offset of tap (0, 0) (negative in the padding)
+  uint32_t xinv[CONV ? RF : 1];  // bit t: tap t lies in the padding
 #pragma unroll
   for (int r = 0; r < RF; ++r) {
     const int32_t n = min(n0 + 16 * r + lr, p.N - 1);
-    xrow[r] = p.X + static_cast<int64_t>(n) * p.C;
+    if constexpr (CONV) {
+      const int32_t img = n / p.HoWo, rem = n - img * p.HoWo;
+      const int32_t oh = rem / p.Wo, ow = rem - oh * p.Wo;
+      const int32_t ih0 = oh * p.sh - p.ph, iw0 = ow * p.sw - p.pw;
+      xoff[r] = ((img * p.H + ih0) * p.W + iw0) * p.Cin * 2;
+      uint32_t inv = 0;
+      int t = 0;
+      for (int kh = 0; kh < p.KH; ++kh)
+        for (int kw = 0; kw < p.KW; ++kw, ++t) {
+          const bool ok = static_cast<uint32_t>(ih0 + kh) < static_cast<uint32_t>(p.H) &&
+                          static_cast<uint32_t>(iw0 + kw) < static_cast<uint32_t>(p.W);
+          inv |= (ok ? 0u : 1u) << t;
+        }
+      xinv[r] = inv;
+    } else {
+      xrow[r] = p.X + static_cast<int64_t>(n) * p.C;
+    }
   }
+  const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint16_t*>(p.X), (short)0, static_cast<int>(CONV ? p.x_bytes : 0), kRsrcWord3);
 
   f32x4_t acc[RF][OF];
 #pragma unroll
@@ -158,8 +196,21 @@ __global__ __launch_bounds__(kThreads) void split_k_kernel(KParams p) {
     for (int j = 0; j < U; ++j) {
       const int32_t s = s0 + kWaves * j;
       if (s < nks) {
+        if constexpr (CONV) {
+          // tap and channel block of the k-step
+          const int32_t t = p.Cin == 32 ? s : static_cast<int32_t>(__umulhi(static_cast<uint32_t>(s), p.spt_mul));
+          const int32_t kh = static_cast<int32_t>(static_cast<uint32_t>(t) * p.kw_mul >> 16), kw = t - kh * p.KW;
+          const int32_t c = lane_c0(s) - t * p.Cin;
+          const int32_t toff = ((kh * p.W + kw) * p.Cin + c) * 2;
 #pragma unroll
-        for (int r = 0; r < RF; ++r) st[j].x[r] = *reinterpret_cast<const u32x4_t*>(xrow[r] + lane_c0(s));
+          for (int r = 0; r < RF; ++r) {
+            const uint32_t off = static_cast<uint32_t>(xoff[r] + toff) | (((xinv[r] >> t) & 1u) << 31);
+            st[j].x[r] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(xr, off, 0, 0));
+          }
+        } else {
+#pragma unroll
+          for (int r = 0; r < RF; ++r) st[j].x[r] = *reinterpret_cast<const u32x4_t*>(xrow[r] + lane_c0(s));
+        }
         if (!WL) {
           const int32_t c0 = lane_c0(s);
 #pragma unroll
@@ -357,12 +408,12 @@ int64_t block_groups(int64_t TO, int64_t G) {
 // Bytes of the staged packed rows (values and indices) of one output block.
 int64_t staged_bytes(int of, int64_t C, int32_t G, int32_t K) { return 3 * block_groups(16 * of, G) * K * C; }
 
-template <int RF, int OF, int K, bool WL>
+template <int RF, int OF, int K, bool WL, bool CONV>
 hipError_t launch_rokw(const KParams& p, int64_t dyn, DType y_t, hipStream_t s) {
   const uint32_t grid = static_cast<uint32_t>(p.tpx) * kXcds;
   static std::atomic<int8_t> lds_set[2][kMaxDevices];
-  const auto kf = &split_k_kernel<RF, OF, K, WL, float>;
-  const auto kb = &split_k_kernel<RF, OF, K, WL, bf16_t>;
+  const auto kf = &split_k_kernel<RF, OF, K, WL, CONV, float>;
+  const auto kb = &split_k_kernel<RF, OF, K, WL, CONV, bf16_t>;
   if (WL) {
     const int limit = static_cast<int>(kLdsMax - red_bytes(RF, OF));
     const hipError_t e = y_t == DType::F32 ? set_lds_limit_once(lds_set[0], reinterpret_cast<const void*>(kf), limit)
@@ -381,7 +432,9 @@ hipError_t launch_rok(const KParams& p, bool wl, int64_t dyn, DType y_t, hipStre
   if constexpr (!tile_fits(RF, OF, K)) {
     return hipErrorInvalidConfiguration;
   } else {
-    return wl ? launch_rokw<RF, OF, K, true>(p, dyn, y_t, s) : launch_rokw<RF, OF, K, false>(p, 0, y_t, s);
+    if (p.KH != 0)
+      return wl ? launch_rokw<RF, OF, K, true, true>(p, dyn, y_t, s) : launch_rokw<RF, OF, K, false, true>(p, 0, y_t, s);
+    return wl ? launch_rokw<RF, OF, K, true, false>(p, dyn, y_t, s) : launch_rokw<RF, OF, K, false, false>(p, 0, y_t, s);
   }
 }
 
@@ -430,12 +483,21 @@ static void split_k_tile(int64_t N, int64_t C, int64_t O, int32_t G, int32_t K, 
   }
 }
 
+// FC products and 1x1 convolutions whose rows are the input pixels.
+static bool plain_rows(const ProductArgs& a) {
+  const ConvGeom& g = a.geom;
+  return !a.conv || (g.KH == 1 && g.KW == 1 && g.sh == 1 && g.sw == 1 && g.ph == 0 && g.pw == 0);
+}
+
 bool split_k_supports(const ProductArgs& a) {
   if (a.x_t != DType::BF16 || a.val_t != DType::BF16) return false;
   if (a.G < 1 || a.G > 256 || a.K < 1 || a.K > 4 || a.K > a.G) return false;
-  if (a.conv) {
+  if (!plain_rows(a)) {
+    // a k-step lies under one tap, every offset is 32-bit and stays below
+    // the out-of-range marker
     const ConvGeom& g = a.geom;
-    if (g.KH != 1 || g.KW != 1 || g.sh != 1 || g.sw != 1 || g.ph != 0 || g.pw != 0) return false;
+    if (!a.ragged || g.KH * g.KW > kMaxTaps || (g.KH * g.KW > 1 && g.Cin % 32 != 0)) return false;
+    if (a.B * g.H * g.W * g.Cin * 2 >= static_cast<int64_t>(kOOB)) return false;
   }
   if (a.N < 1 || a.C < 32 || a.C % 8 != 0 || a.O % 8 != 0) return false;
   if (!a.ragged && (a.C % 32 != 0 || a.O % 16 != 0)) return false;
@@ -464,6 +526,24 @@ hipError_t launch_split_k(const ProductArgs& a, hipStream_t s) {
   p.O = static_cast<int32_t>(a.O);
   p.G = a.G;
   p.relu = a.relu;
+  if (!plain_rows(a)) {
+    const ConvGeom& g = a.geom;
+    p.x_bytes = static_cast<uint32_t>(a.B * g.H * g.W * g.Cin * 2);
+    p.H = g.H;
+    p.W = g.W;
+    p.Cin = g.Cin;
+    p.KH = g.KH;
+    p.KW = g.KW;
+    p.sh = g.sh;
+    p.sw = g.sw;
+    p.ph = g.ph;
+    p.pw = g.pw;
+    p.HoWo = g.Ho * g.Wo;
+    p.Wo = g.Wo;
+    // (a single tap is tap 0 whatever the quotient of its ragged k-steps)
+    p.spt_mul = g.KH * g.KW > 1 ? static_cast<uint32_t>((uint64_t(1) << 32) / static_cast<uint32_t>(g.Cin / 32) + 1) : 0u;
+    p.kw_mul = (1u << 16) / static_cast<uint32_t>(g.KW) + 1;
+  }
   p.nob = static_cast<int32_t>((a.O + 16 * of - 1) / (16 * of));
   const int64_t tiles = (a.N + 16 * rf - 1) / (16 * rf) * p.nob;
   if (tiles > (int64_t(1) << 30)) return hipErrorInvalidConfiguration;

@@ -229,7 +229,10 @@ def test_conv_tap_tile_epilogue(y_dtype):
 @pytest.mark.parametrize("B,H,W,Cin,O,k,stride,pad,G,K", [
     (9, 30, 30, 64, 64, 3, 2, 1, 8, 2), (20, 28, 28, 64, 96, 3, 1, 1, 8, 2),  # 64- and 96-output tiles, taps
     (40, 17, 19, 136, 72, 1, 2, 0, 8, 4), (8, 30, 31, 72, 200, 1, 1, 1, 8, 2),  # strided / padded 1x1, short chunk
-    (3, 14, 14, 256, 256, 3, 1, 1, 8, 2), (2, 9, 9, 64, 136, 3, 1, 1, 8, 4),  # two teams starting inside a filter row
+    (9, 14, 14, 256, 256, 3, 1, 1, 8, 2), (60, 9, 9, 64, 136, 3, 1, 1, 8, 4),  # two teams starting inside a filter row
+    # split-reduction: taps of 1, 3 and 8 k-steps, strides, no and wide padding, ragged outputs, a strided short reduction
+    (1, 14, 14, 256, 256, 3, 1, 1, 8, 2), (2, 15, 13, 32, 48, 5, 2, 2, 4, 1), (1, 9, 20, 96, 40, 3, 2, 0, 8, 3),
+    (3, 11, 7, 72, 136, 1, 2, 0, 8, 4), (1, 7, 7, 512, 512, 3, 1, 1, 8, 4), (1, 6, 5, 64, 64, 3, 2, 2, 16, 2),
 ])
 def test_conv_ragged_auto(B, H, W, Cin, O, k, stride, pad, G, K):
     """Convolutions AUTO gives to the tap-chunk and split-reduction kernels' ragged forms."""
