@@ -156,3 +156,27 @@ def test_td_mask_ties_every_candidate_count(G):
     W = rng.choice(np.array([0.0, -0.0, 1.0, -1.0, 2.0, np.inf, -np.inf], np.float32), (O, C))
     for n_t in range(G + 1):
         run_mask(W, G, n_t, rand_bits((O, C), n_t), 0.5, torch.bfloat16)
+
+
+@pytest.mark.parametrize("N,C,O,G,K", [
+    # 128 x 128 tiles: ragged edges, one to five steps (the DMA ring fills at three), the last step partial
+    (32, 136, 64, 8, 2), (33, 8, 264, 4, 1), (96, 256, 128, 16, 4), (150, 392, 200, 8, 8), (129, 120, 192, 64, 9),
+    # 128 % G == 0 but 64 % G != 0, and enough tiles: 256 x 256
+    (70, 300 // 4 * 4, 256, 128, 5), (40, 4096, 2560, 16, 2), (100, 4104, 2568, 8, 1),
+])
+def test_grad_packed_tiles(N, C, O, G, K):
+    need_gpu()
+    from paper_1910_11971_amd import cci
+    g = torch.Generator(device=DEV)
+    g.manual_seed(N + C + O)
+    dY = torch.randn(N, O, device=DEV, generator=g).bfloat16()
+    X = torch.randn(N, C, device=DEV, generator=g).bfloat16()
+    _, idx = cci.pack(torch.randn(O, C, device=DEV, generator=g), G, K)
+    out = Guarded((O // G, K, C), torch.float32)
+    cci.grad_packed(dY, X, idx, G, out=out.t)
+    torch.cuda.synchronize()
+    out.check("dvals")
+    ref = (dY.double().t() @ X.double()).view(O // G, G, C).gather(1, idx.long())
+    mag = (dY.double().abs().t() @ X.double().abs()).view(O // G, G, C).gather(1, idx.long())
+    # fp32 sums of N products in any order: at most N rounding steps of 2^-24 of the absolute sum
+    assert ((out.t.double() - ref).abs() <= (N + 1) * 2.0 ** -24 * mag).all()
