@@ -109,14 +109,15 @@ __device__ __forceinline__ u32x4_t sdesc(const void* base, uint32_t bytes) {
   return u32x4_t{rfl(static_cast<uint32_t>(a)), rfl(static_cast<uint32_t>(a >> 32) & 0xffffu), rfl(bytes),
                  static_cast<uint32_t>(kRsrcWord3)};
 }
-__device__ __forceinline__ u32x4_t load_x4(const u32x4_t d, uint32_t off) {
+// (soff: a wave-uniform byte offset)
+__device__ __forceinline__ u32x4_t load_x4(const u32x4_t d, uint32_t off, uint32_t soff) {
   u32x4_t v;
-  asm volatile("buffer_load_dwordx4 %0, %1, %2, 0 offen" : "=v"(v) : "v"(off), "s"(d) : "memory");
+  asm volatile("buffer_load_dwordx4 %0, %1, %2, %3 offen" : "=v"(v) : "v"(off), "s"(d), "s"(soff) : "memory");
   return v;
 }
-__device__ __forceinline__ u32x2_t load_x2(const u32x4_t d, uint32_t off) {
+__device__ __forceinline__ u32x2_t load_x2(const u32x4_t d, uint32_t off, uint32_t soff) {
   u32x2_t v;
-  asm volatile("buffer_load_dwordx2 %0, %1, %2, 0 offen" : "=v"(v) : "v"(off), "s"(d) : "memory");
+  asm volatile("buffer_load_dwordx2 %0, %1, %2, %3 offen" : "=v"(v) : "v"(off), "s"(d), "s"(soff) : "memory");
   return v;
 }
 
@@ -170,7 +171,7 @@ __device__ __forceinline__ uint32_t trow(uint32_t o) { return ((o >> 4) << 11) |
 template <typename YT, int UPL, bool FULL, bool BIGG, bool MASK, int KS, int TO>
 __device__ __forceinline__ void tap_tile_body(const TParams& p, uint8_t* const lds0) {
   constexpr int NX = kNX;
-  constexpr int RW = NX - 1;         // packed-unit ring stages: W(m) is issued with X(m)
+  constexpr int RW = 2;              // packed-unit ring stages
   constexpr int OT = TO / 32;        // 16-output tiles per wave
   constexpr int RPW = TO / 4;        // weight-tile rows a wave builds
   constexpr int WB = wb_bytes(TO);   // one weight tile
@@ -233,42 +234,56 @@ __device__ __forceinline__ void tap_tile_body(const TParams& p, uint8_t* const l
       xinv[i] = inv;
     }
   }
-  // Tap cursor of the next chunk to DMA: t = tap, cb = channel block,
-  // kw = column of the tap, off = byte offset of (tap, block) from the
-  // pixel's tap-(0, 0) block.  The next block of a tap, and the first block
-  // of the next tap in the row, are both 128 bytes further.
+  // Tap cursor of the next chunk to DMA: t = tap (row kh, column kw of the
+  // filter), cb = channel block.  The lane's byte offsets under that tap (bit
+  // 31 set where the tap falls into the padding) change with the tap only, the
+  // channel block is the loads' uniform offset: they are kept (xv) where the
+  // registers allow it (one packed unit per lane), else made per chunk.
+  constexpr bool KEEP = UPL == 1;
   int cur_t = ch0 / p.cpt, cur_cb = ch0 - cur_t * p.cpt;
-  const int cur_kh = cur_t / p.KW;
-  int cur_kw = cur_t - cur_kh * p.KW;
-  int32_t cur_off = ((cur_kh * p.W + cur_kw) * p.Cin + cur_cb * kCK) * 2;
-  const int32_t row_skip = (p.W - p.KW) * p.Cin * 2;
-  // (From chunk `full` on the column blocks past C read zero, in X here and in
+  int cur_kh = cur_t / p.KW, cur_kw = cur_t - cur_kh * p.KW;
+  uint32_t xv[KEEP ? 4 : 1];
+  const auto tap_off = [&](int i) {
+    return static_cast<uint32_t>(xbase[i] + (cur_kh * p.W + cur_kw) * p.Cin * 2) | (((xinv[i] >> cur_t) & 1u) << 31);
+  };
+  auto set_tap = [&] {
+    if constexpr (KEEP) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) xv[i] = tap_off(i);
+    }
+  };
+  set_tap();
+  // From chunk `full` on the column blocks past C read zero, in X here and in
   // the packed rows in load_w, so that a neighbouring row's infinity cannot
-  // meet a zero.)
+  // meet a zero.  (TAIL: the chunk may be such a one; a dead chunk after them
+  // leaves every offset out of range.)
   const int rag = p.full - ch0;  // the first chunk of this team that is not whole
   const auto live_k8 = [&](int ch) { return ch == rag ? p.rag_k8 : 0; };
-  auto issue_x = [&](int ch, int buf) {
+  auto issue_x = [&](int ch, int buf, auto tail) {
     uint8_t* dst = lds + buf * kXB + w * 4096;
-    if (ch >= rag) {
+    if constexpr (decltype(tail)::value) {
+      if (ch >= rag) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int q = (4 * w + i) * 8 + (lane >> 3);
-        xinv[i] = ((lane & 7) ^ ((q >> 1) & 7)) < live_k8(ch) ? xinv[i] : ~0u;
+        for (int i = 0; i < 4; ++i) {
+          const int q = (4 * w + i) * 8 + (lane >> 3);
+          const bool live = ((lane & 7) ^ ((q >> 1) & 7)) < live_k8(ch);
+          xinv[i] = live ? xinv[i] : ~0u;
+          if constexpr (KEEP) xv[i] = live ? xv[i] : kOOB;
+        }
       }
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t off = static_cast<uint32_t>(xbase[i] + cur_off) | (((xinv[i] >> cur_t) & 1u) << 31);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lds_void_t*)(dst + i * 1024), 16, off, 0, 0, 0);
-    }
-    cur_off += 128;
+    for (int i = 0; i < 4; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lds_void_t*)(dst + i * 1024), 16, KEEP ? xv[KEEP ? i : 0] : tap_off(i),
+                                               cur_cb * (kCK * 2), 0, 0);
     if (++cur_cb == p.cpt) {
       cur_cb = 0;
       ++cur_t;
       if (++cur_kw == p.KW) {
         cur_kw = 0;
-        cur_off += row_skip;
+        ++cur_kh;
       }
+      set_tap();
     }
   };
 
@@ -279,12 +294,11 @@ __device__ __forceinline__ void tap_tile_body(const TParams& p, uint8_t* const l
   const u32x4_t vd = sdesc(p.vals, p.v_bytes), id = sdesc(p.idx, p.i_bytes);
   // The lanes of one packed row write neighbouring column blocks whose
   // 16-byte row segments all start on the same bank, so at step e lane l
-  // writes element e ^ m, m = l % 8, of its unit: one instruction's two-byte
-  // stores spread over four times as many banks.  A unit's values and
-  // indices are permuted once (permute_unit) so that step e reads them at
-  // fixed positions.
-  const uint32_t m = static_cast<uint32_t>(lane & 7);
-  const uint32_t bsel = 0x03020100u ^ ((m & 3u) * 0x01010101u);  // byte j <- byte j ^ (m % 4)
+  // writes element e ^ m, m = 2 (l % 4), of its unit: one instruction's
+  // two-byte stores spread over four times as many banks (the halves of a
+  // bank word need no spreading).  A unit's values and indices are permuted
+  // once (permute_unit) so that step e reads them at fixed positions.
+  const uint32_t m = 2u * static_cast<uint32_t>(lane & 3);
   uint32_t voff[UPL], ioff[UPL], ubase[UPL];
   bool uok[UPL];
 #pragma unroll
@@ -306,16 +320,18 @@ __device__ __forceinline__ void tap_tile_body(const TParams& p, uint8_t* const l
   // chunks j with j % RW == k (the index is always a compile-time constant).
   u32x4_t pv[RW][UPL];
   u32x2_t pi[RW][UPL];
-  auto load_w = [&](int ch, auto kc) {
+  auto load_w = [&](int ch, auto kc, auto tail) {
     constexpr int k = decltype(kc)::value;
-    if (ch >= rag && (lane & 7) >= live_k8(ch)) {  // (c8 of every unit of a lane is lane % 8)
+    if constexpr (decltype(tail)::value) {
+      if (ch >= rag && (lane & 7) >= live_k8(ch)) {  // (c8 of every unit of a lane is lane % 8)
 #pragma unroll
-      for (int u = 0; u < UPL; ++u) voff[u] = ioff[u] = kOOB;
+        for (int u = 0; u < UPL; ++u) voff[u] = ioff[u] = kOOB;
+      }
     }
 #pragma unroll
     for (int u = 0; u < UPL; ++u) {
-      pv[k][u] = load_x4(vd, voff[u] + static_cast<uint32_t>(ch0 + ch) * (kCK * 2));
-      if constexpr (!FULL) pi[k][u] = load_x2(id, ioff[u] + static_cast<uint32_t>(ch0 + ch) * kCK);
+      pv[k][u] = load_x4(vd, voff[u], static_cast<uint32_t>(ch0 + ch) * (kCK * 2));
+      if constexpr (!FULL) pi[k][u] = load_x2(id, ioff[u], static_cast<uint32_t>(ch0 + ch) * kCK);
     }
   };
   auto w_fence = [&](auto kc) { fence_stage<decltype(kc)::value, FULL>(pv, pi); };
@@ -329,10 +345,9 @@ __device__ __forceinline__ void tap_tile_body(const TParams& p, uint8_t* const l
         x = u32x2_t{x[1], x[0]};
       }
       if (m & 2u) d = u32x4_t{d[1], d[0], d[3], d[2]};
-      const uint32_t hs = 16u * (m & 1u);
-      pv[k][u] = u32x4_t{__builtin_amdgcn_alignbit(d[0], d[0], hs), __builtin_amdgcn_alignbit(d[1], d[1], hs),
-                         __builtin_amdgcn_alignbit(d[2], d[2], hs), __builtin_amdgcn_alignbit(d[3], d[3], hs)};
-      pi[k][u] = u32x2_t{__builtin_amdgcn_perm(x[0], x[0], bsel), __builtin_amdgcn_perm(x[1], x[1], bsel)};
+      pv[k][u] = d;
+      pi[k][u] = u32x2_t{__builtin_amdgcn_alignbit(x[0], x[0], 8u * (m & 2u)),
+                         __builtin_amdgcn_alignbit(x[1], x[1], 8u * (m & 2u))};
     }
   };
   // tile offset of row rr of a group, relative to its first row
@@ -351,8 +366,14 @@ __device__ __forceinline__ void tap_tile_body(const TParams& p, uint8_t* const l
     } else {
       // row within the group (masked to the group's span: a bad index byte
       // cannot address past the tile)
-      const uint32_t rr = (pi[k][u][e >> 2] >> (8 * (e & 3))) & (BIGG ? 31u : 15u);
-      *reinterpret_cast<uint16_t*>(tb + ((ubase[u] + grow(rr)) ^ (2u * static_cast<uint32_t>(e)))) =
+      // (bits 1..3 of ubase hold 2 m and rows move bits 4 and up: element e
+      // ^ m's byte offset is 2 e flipped into them, before or after the row is
+      // added.  Before makes it a loop constant per e, one instruction less,
+      // where the registers hold eight of them: one unit per lane.)
+      const uint32_t rr = __builtin_amdgcn_ubfe(pi[k][u][e >> 2], 8 * (e & 3), BIGG ? 5 : 4);
+      const uint32_t at = UPL == 1 ? (ubase[u] ^ (2u * static_cast<uint32_t>(e))) + grow(rr)
+                                   : (ubase[u] + grow(rr)) ^ (2u * static_cast<uint32_t>(e));
+      *reinterpret_cast<uint16_t*>(tb + at) =
           static_cast<uint16_t>(pv[k][u][e >> 1] >> (16 * (e & 1)));
     }
   };
@@ -379,118 +400,129 @@ __device__ __forceinline__ void tap_tile_body(const TParams& p, uint8_t* const l
 
   // ---- pipeline -----------------------------------------------------------------
   // A wave's vector-memory operations are issued in pairs W(m), X(m) (packed
-  // units into ring stage m % RW, activations into buffer m % NX), m = 0 ..
-  // RW - 1 before the loop, then m = j + RW during chunk j: into the stage
-  // and the buffer that chunk j-1 released.  Tile j+1 is built during chunk j
-  // from stage (j+1) % RW.  Loads complete in issue order, so "X(j+1) has
-  // landed" (and W(j+1) with it) is "at most the pairs issued after it are in
-  // flight".
+  // units into ring stage m % 2, activations into buffer m % 3): m = 0, 1, 2
+  // before the loop, then m = j + 3 in the second half of chunk j: chunk j has
+  // released the buffer, and tile j+1, built in its first half, the stage.
+  // Loads complete in issue order, so "W(j+1) has landed" is "at most X(j+1)
+  // and the pairs issued after it are in flight".
   constexpr int kPair = (FULL ? 1 : 2) * UPL + 4;  // vector-memory operations of one pair
-  auto wait_pairs = [](int n) {  // at most n pairs in flight (n < RW)
-    switch (n) {
-      case 0: wait_vm<0>(); break;
-      case 1: wait_vm<kPair>(); break;
-      case 2: wait_vm<(RW > 2 ? 2 : 0) * kPair>(); break;
-      case 3: wait_vm<(RW > 3 ? 3 : 0) * kPair>(); break;
-      default: wait_vm<(RW > 4 ? 4 : 0) * kPair>(); break;
-    }
-  };
-  static_assert(RW <= 5 && (RW - 1) * kPair < 64, "vmcnt range");
+  static_assert(2 * kPair < 64, "vmcnt range");
+  const auto wbuf = [&](int j) { return lds + NX * kXB + (j & 1) * WB; };
+  bf16x8_t fa[OT], fb[4], ga[OT], gb[4];  // fragments of k-step 0, of k-step 1
+  const auto read_fa = [&](int j, int q) { fa[q] = ld(wbuf(j) + wo * (OT * 2048) + lane * 16 + (2 * q) * 1024); };
+  const auto read_fb = [&](int j, int q) { fb[q] = ld(lds + (j % NX) * kXB + wp * 8192 + q * 2048 + boff0); };
   for_k(std::make_integer_sequence<int, RW>{}, [&](auto kc) {
     if (decltype(kc)::value < nch) {
-      load_w(decltype(kc)::value, kc);
-      issue_x(decltype(kc)::value, decltype(kc)::value % NX);
+      load_w(decltype(kc)::value, kc, std::integral_constant<bool, true>{});
+      issue_x(decltype(kc)::value, decltype(kc)::value, std::integral_constant<bool, true>{});
     }
   });
-  wait_pairs(min(RW, nch) - 1);  // W(0), X(0)
+  if (nch > 1) wait_vm<kPair>(); else wait_vm<0>();  // W(0), X(0)
   w_fence(std::integral_constant<int, 0>{});
   for (int u = 0; u < UPL; ++u) permute_unit(std::integral_constant<int, 0>{}, u);
   if constexpr (!FULL)
-    for (int i = 0; i < RPW / 8; ++i) zero_piece(lds + NX * kXB, i);
+    for (int i = 0; i < RPW / 4; ++i) zero_piece(wbuf(i / (RPW / 8)), i % (RPW / 8));  // both tiles
   for (int u = 0; u < UPL; ++u)
-    for (int e = 0; e < 8; ++e) scatter_e(lds + NX * kXB, std::integral_constant<int, 0>{}, u, e);
+    for (int e = 0; e < 8; ++e) scatter_e(wbuf(0), std::integral_constant<int, 0>{}, u, e);
+  if (nch > 2) {
+    load_w(2, std::integral_constant<int, 0>{}, std::integral_constant<bool, true>{});
+    issue_x(2, 2, std::integral_constant<bool, true>{});
+  }
   lds_barrier();
+#pragma unroll
+  for (int q = 0; q < OT; ++q) read_fa(0, q);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) read_fb(0, q);
 
-  // Chunk j with j % RW == k.  Its 32 MFMAs (k-step 0, then 1) are issued
-  // one by one with the other work of the chunk placed between them (one
-  // wave per SIMD issues in order):
-  //   k-step 0: the k-step-1 fragments (slots 0-7), the zero fill of tile
-  //     j+1 (slots 8-11), the pair W(j+RW), X(j+RW) (slots 12-15);
-  //   then wait for W(j+1) and X(j+1);
-  //   k-step 1: the kept weights of tile j+1 (8 UPL two-byte stores spread
-  //     over the 16 slots);
-  //   barrier: tile j+1 and X(j+1) are complete in every wave.
-  // ST: the pair and tile j+1 exist and the wait is the steady-state one.
-  auto step = [&](int j, auto kc, auto st) {
-    constexpr int k = decltype(kc)::value;
-    constexpr int k1 = (k + 1) % RW;
+  // Chunk j with j % 2 == k in buffer x, its k-step-0 fragments in registers.  The MFMAs
+  // are issued one by one with the other work placed between them (a wave
+  // issues in order):
+  //   k-step 0: the k-step-1 fragments, then the kept weights of tile j+1 (8
+  //     UPL two-byte stores) into rows zeroed a chunk ago;
+  //   barrier: chunk j's fragments are in registers everywhere, tile j+1 and
+  //     X(j+1) are complete;
+  //   k-step 1: the k-step-0 fragments of chunk j+1, the zero fill of tile
+  //     j+2 (in tile j's rows), the pair W(j+3), X(j+3).
+  // So a fragment read always has half a chunk of MFMAs to land in: with the
+  // barrier after the chunk, every chunk began with an exposed LDS round trip
+  // (us, before / with it and fewer address instructions: 4096 x 2048 -> 2048
+  // 47 / 43; 3000 x 3008 -> 3008 87 / 80; 300 x 4096 -> 4096 33.6 / 31.5).
+  // ST: the steady state, where chunks j+1 .. j+3 exist and are whole.
+  auto step = [&](int j, int x, auto kc, auto st) {
+    constexpr int k1 = (decltype(kc)::value + 1) % RW;
     constexpr bool ST = decltype(st)::value;
-    const bool issue = ST || j + RW < nch;
-    const bool next = ST || j + 1 < nch;
-    const uint8_t* xb = lds + (j % NX) * kXB + wp * 8192;
-    const uint8_t* wb = lds + NX * kXB + (j & 1) * WB + wo * (OT * 2048) + lane * 16;
-    uint8_t* tb = lds + NX * kXB + ((j + 1) & 1) * WB;
-    bf16x8_t fa[OT], fb[4], ga[OT], gb[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) fb[q] = ld(xb + q * 2048 + boff0);
-#pragma unroll
-    for (int q = 0; q < OT; ++q) fa[q] = ld(wb + (2 * q) * 1024);
-#pragma unroll
-    for (int i = 0; i < NMF; ++i) {
-      mfma_acc(acc[i / OT][i % OT], fa[i % OT], fb[i / OT]);
-      __builtin_amdgcn_sched_barrier(0);
-      if (i < OT) ga[i] = ld(wb + (2 * i + 1) * 1024);
-      if (i >= OT && i < OT + 4) gb[i - OT] = ld(xb + (i - OT) * 2048 + boff1);
-      if constexpr (!FULL) {
-        if (i >= NMF / 2 && i < NMF / 2 + RPW / 8 && next) zero_piece(tb, i - NMF / 2);
-      }
-      if (i == NMF - 4 && issue) load_w(j + RW, kc);
-      if (i == NMF - 3 && issue) issue_x(j + RW, (j + RW) % NX);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    const bool next = ST || j + 1 < nch, next2 = ST || j + 2 < nch, issue = ST || j + NX < nch;
+    const uint8_t* xb = lds + x * kXB + wp * 8192;
+    const uint8_t* xn = lds + (x == NX - 1 ? 0 : x + 1) * kXB + wp * 8192;
+    const uint8_t* wb = wbuf(j) + wo * (OT * 2048) + lane * 16;
     if (next) {
-      if constexpr (ST) {
-        wait_vm<(RW - 1) * kPair>();
-      } else {
-        wait_pairs(min(j + RW, nch - 1) - (j + 1));
-      }
+      if (next2) wait_vm<kPair + 4>(); else wait_vm<4>();  // W(j+1)
       w_fence(std::integral_constant<int, k1>{});
 #pragma unroll
       for (int u = 0; u < UPL; ++u) permute_unit(std::integral_constant<int, k1>{}, u);
     }
 #pragma unroll
     for (int i = 0; i < NMF; ++i) {
-      mfma_acc(acc[i / OT][i % OT], ga[i % OT], gb[i / OT]);
+      mfma_acc(acc[i / OT][i % OT], fa[i % OT], fb[i / OT]);
       __builtin_amdgcn_sched_barrier(0);
+      if (i < OT) ga[i] = ld(wb + (2 * i + 1) * 1024);
+      if (i >= OT && i < OT + 4) gb[i - OT] = ld(xb + (i - OT) * 2048 + boff1);
       if (next) {
         // step q of the 8 UPL stores goes to slot q * NMF / (8 UPL)
 #pragma unroll
         for (int q = 0; q < 8 * UPL; ++q)
-          if ((q * NMF) / (8 * UPL) == i) scatter_e(tb, std::integral_constant<int, k1>{}, q >> 3, q & 7);
+          if ((q * NMF) / (8 * UPL) == i) scatter_e(wbuf(j + 1), std::integral_constant<int, k1>{}, q >> 3, q & 7);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    lds_barrier();
+    if (next) {
+      if (next2) wait_vm<kPair>(); else wait_vm<0>();  // X(j+1)
+      lds_barrier();
+    }
+#pragma unroll
+    for (int i = 0; i < NMF; ++i) {
+      mfma_acc(acc[i / OT][i % OT], ga[i % OT], gb[i / OT]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (next) {
+        if (i < OT) read_fa(j + 1, i);
+        if (i < 4) fb[i] = ld(xn + i * 2048 + boff0);
+      }
+      if constexpr (!FULL) {
+        if (i >= NMF / 2 && i < NMF / 2 + RPW / 8 && next2) zero_piece(wbuf(j), i - NMF / 2);
+      }
+      if (i == NMF - 4 && issue) load_w(j + NX, std::integral_constant<int, k1>{}, std::integral_constant<bool, !ST>{});
+      if (i == NMF - 3 && issue) issue_x(j + NX, x, std::integral_constant<bool, !ST>{});
+      __builtin_amdgcn_sched_barrier(0);
+    }
   };
-  // RW chunks per iteration of the steady state, so every ring stage index
-  // is a constant; the tail (fewer than 2 RW chunks) starts again at stage 0.
-  int j = 0;
+  // two chunks per iteration of the steady state, so every ring stage is a
+  // constant; the tail (up to six chunks: the last two may not be whole)
+  // starts again at stage 0.  (A loop, not six copies: straight-line code is
+  // fetched cold by every workgroup.)
+  int j = 0, x = 0;
+  const auto advance = [&] { x = x == NX - 1 ? 0 : x + 1; };
+  const int whole = min(nch, rag);
 #pragma unroll 1
-  for (; j + 2 * RW - 1 < nch; j += RW)
-    for_k(std::make_integer_sequence<int, RW>{},
-          [&](auto kc) { step(j + decltype(kc)::value, kc, std::integral_constant<bool, true>{}); });
-  for_k(std::make_integer_sequence<int, 2 * RW - 1>{}, [&](auto qc) {
-    constexpr int q = decltype(qc)::value;
-    if (j + q < nch) step(j + q, std::integral_constant<int, q % RW>{}, std::integral_constant<bool, false>{});
-  });
+  for (; j + NX + 1 < whole; j += RW)
+    for_k(std::make_integer_sequence<int, RW>{}, [&](auto kc) {
+      step(j + decltype(kc)::value, x, kc, std::integral_constant<bool, true>{});
+      advance();
+    });
+#pragma unroll 1
+  for (; j < nch; j += RW)
+    for_k(std::make_integer_sequence<int, RW>{}, [&](auto kc) {
+      constexpr int q = decltype(kc)::value;
+      if (q == 0 || j + q < nch) step(j + q, x, kc, std::integral_constant<bool, false>{});
+      advance();
+    });
+  lds_barrier();  // every wave has its last fragments: the operand buffers are free
 
   // ---- fused epilogue -----------------------------------------------------------
   // A wave parks its 64 / KS pixels x TO/2 outputs (fp32) in its own LDS region
   // (pitch TO/2 * 4 + 16 bytes: conflict-free both ways) and reads them back
   // by pixel rows: a lane then owns 8 consecutive outputs of one pixel (LPR
   // lanes cover the wave's TO/2), applies scale / bias / residual / ReLU in
-  // fp32, rounds once and stores 16 (bf16) or 32 bytes.  (The loop's last
-  // barrier has released the operand buffers.)  With two teams, wave w of
+  // fp32, rounds once and stores 16 (bf16) or 32 bytes.  With two teams, wave w of
   // team h finishes pixel tiles 2 h, 2 h + 1: it leaves its partial sums of
   // the other two tiles to wave w of the other team.
   constexpr int LPR = TO / 16;   // lanes per pixel row
@@ -515,6 +547,15 @@ __device__ __forceinline__ void tap_tile_body(const TParams& p, uint8_t* const l
     const uint32_t px = pb * kTP + static_cast<uint32_t>(wp * 64 + 16 * NPT * team + RPP * rr + lane / LPR);
     return px < static_cast<uint32_t>(p.N) && o_ok ? (px * static_cast<uint32_t>(p.O) + o) * ysz : kOOB;
   };
+  f32x4_t sc0{1.f, 1.f, 1.f, 1.f}, sc1{1.f, 1.f, 1.f, 1.f}, bi0{0.f, 0.f, 0.f, 0.f}, bi1{0.f, 0.f, 0.f, 0.f};
+  if (p.scale && o_ok) {
+    sc0 = *reinterpret_cast<const f32x4_t*>(p.scale + o);
+    sc1 = *reinterpret_cast<const f32x4_t*>(p.scale + o + 4);
+  }
+  if (p.bias && o_ok) {
+    bi0 = *reinterpret_cast<const f32x4_t*>(p.bias + o);
+    bi1 = *reinterpret_cast<const f32x4_t*>(p.bias + o + 4);
+  }
   // bf16 residual: all rows' 16-byte pieces are requested before the
   // accumulators are parked (one load latency, not one per row)
   u32x4_t rres[NPS];
@@ -556,15 +597,6 @@ __device__ __forceinline__ void tap_tile_body(const TParams& p, uint8_t* const l
           for (int ot = 0; ot < OT; ++ot) *slot(stg, q, ot) += acc[NPT * H + q][ot];
       }
     });
-  }
-  f32x4_t sc0{1.f, 1.f, 1.f, 1.f}, sc1{1.f, 1.f, 1.f, 1.f}, bi0{0.f, 0.f, 0.f, 0.f}, bi1{0.f, 0.f, 0.f, 0.f};
-  if (p.scale && o_ok) {
-    sc0 = *reinterpret_cast<const f32x4_t*>(p.scale + o);
-    sc1 = *reinterpret_cast<const f32x4_t*>(p.scale + o + 4);
-  }
-  if (p.bias && o_ok) {
-    bi0 = *reinterpret_cast<const f32x4_t*>(p.bias + o);
-    bi1 = *reinterpret_cast<const f32x4_t*>(p.bias + o + 4);
   }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this wave's staging writes have landed
 #pragma unroll
