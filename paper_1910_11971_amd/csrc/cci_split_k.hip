@@ -67,9 +67,11 @@ struct KParams {
   int32_t nob;    // output blocks (O / (16 OF), rounded up)
   int32_t tiles;  // row blocks x output blocks
   int32_t tpx;    // tiles per XCD (ceil(tiles / 8))
+  Div fd_nob, fd_g;
   // convolutions read through implicit im2col
   uint32_t x_bytes;
-  int32_t H, W, Cin, KH, KW, sh, sw, ph, pw, HoWo, Wo;
+  int32_t H, W, Cin, KH, KW, sh, sw, ph, pw;
+  Div fd_howo, fd_wo;
   uint32_t spt_mul;  // k-step / (Cin / 32) == mulhi(k-step, spt_mul) (Cin == 32: unused)
   uint32_t kw_mul;   // tap / KW == (tap * kw_mul) >> 16
 };
@@ -130,7 +132,8 @@ __global__ __launch_bounds__(kThreads) void split_k_kernel(KParams p) {
   const int32_t b = static_cast<int32_t>(blockIdx.x);
   const int32_t t = (b % kXcds) * p.tpx + b / kXcds;
   if (t >= p.tiles) return;  // whole workgroup: before any barrier
-  const int32_t rb = t / p.nob, ob = t - rb * p.nob;
+  uint32_t obu;
+  const int32_t rb = static_cast<int32_t>(divmod(static_cast<uint32_t>(t), p.fd_nob, obu)), ob = static_cast<int32_t>(obu);
   const int32_t w = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / 64);
   const int32_t lane = static_cast<int32_t>(threadIdx.x) % 64;
   const int32_t lr = lane % 16, lq = lane / 16;
@@ -138,7 +141,8 @@ __global__ __launch_bounds__(kThreads) void split_k_kernel(KParams p) {
 
   // per output fragment: the lane's group row base (in the packed arrays, or
   // in the staged copy of groups g_lo ..) and slot
-  const int32_t g_lo = o0 / p.G;
+  uint32_t slot;
+  const int32_t g_lo = static_cast<int32_t>(divmod(static_cast<uint32_t>(o0), p.fd_g, slot));
   int64_t gbase[OF];
   uint32_t rrx[OF];
 #pragma unroll
@@ -146,8 +150,8 @@ __global__ __launch_bounds__(kThreads) void split_k_kernel(KParams p) {
     // (a lane past O, in a ragged last block, reads the last output's group:
     // its sums are never stored)
     const int32_t o = min(o0 + 16 * f + lr, p.O - 1);
-    const int32_t g = o / p.G;
-    rrx[f] = static_cast<uint32_t>(o - g * p.G) * 0x01010101u;
+    const int32_t g = static_cast<int32_t>(divmod(static_cast<uint32_t>(o), p.fd_g, slot));
+    rrx[f] = slot * 0x01010101u;
     gbase[f] = static_cast<int64_t>(WL ? g - g_lo : g) * K * p.C;
   }
   // X rows past N read row N - 1 (their sums are never stored)
@@ -158,19 +162,18 @@ __global__ __launch_bounds__(kThreads) void split_k_kernel(KParams p) {
   for (int r = 0; r < RF; ++r) {
     const int32_t n = min(n0 + 16 * r + lr, p.N - 1);
     if constexpr (CONV) {
-      const int32_t img = n / p.HoWo, rem = n - img * p.HoWo;
-      const int32_t oh = rem / p.Wo, ow = rem - oh * p.Wo;
-      const int32_t ih0 = oh * p.sh - p.ph, iw0 = ow * p.sw - p.pw;
-      xoff[r] = ((img * p.H + ih0) * p.W + iw0) * p.Cin * 2;
-      uint32_t inv = 0;
-      int t = 0;
+      uint32_t rem, ow;
+      const uint32_t img = divmod(static_cast<uint32_t>(n), p.fd_howo, rem);
+      const uint32_t oh = divmod(rem, p.fd_wo, ow);
+      const int32_t ih0 = static_cast<int32_t>(oh) * p.sh - p.ph, iw0 = static_cast<int32_t>(ow) * p.sw - p.pw;
+      xoff[r] = ((static_cast<int32_t>(img) * p.H + ih0) * p.W + iw0) * p.Cin * 2;
+      // columns kw of the filter inside the image: lo <= kw < hi
+      const int32_t lo = max(0, -iw0), hi = min(p.KW, p.W - iw0);
+      const uint32_t row = hi > lo ? (hi < 32 ? (1u << hi) - 1u : ~0u) & (~0u << lo) : 0u;
+      uint32_t ok = 0;
       for (int kh = 0; kh < p.KH; ++kh)
-        for (int kw = 0; kw < p.KW; ++kw, ++t) {
-          const bool ok = static_cast<uint32_t>(ih0 + kh) < static_cast<uint32_t>(p.H) &&
-                          static_cast<uint32_t>(iw0 + kw) < static_cast<uint32_t>(p.W);
-          inv |= (ok ? 0u : 1u) << t;
-        }
-      xinv[r] = inv;
+        ok |= static_cast<uint32_t>(ih0 + kh) < static_cast<uint32_t>(p.H) ? row << (kh * p.KW) : 0u;
+      xinv[r] = ~ok;
     } else {
       xrow[r] = p.X + static_cast<int64_t>(n) * p.C;
     }
@@ -538,13 +541,15 @@ hipError_t launch_split_k(const ProductArgs& a, hipStream_t s) {
     p.sw = g.sw;
     p.ph = g.ph;
     p.pw = g.pw;
-    p.HoWo = g.Ho * g.Wo;
-    p.Wo = g.Wo;
+    p.fd_howo = make_div(static_cast<int64_t>(g.Ho) * g.Wo);
+    p.fd_wo = make_div(g.Wo);
     // (a single tap is tap 0 whatever the quotient of its ragged k-steps)
     p.spt_mul = g.KH * g.KW > 1 ? static_cast<uint32_t>((uint64_t(1) << 32) / static_cast<uint32_t>(g.Cin / 32) + 1) : 0u;
     p.kw_mul = (1u << 16) / static_cast<uint32_t>(g.KW) + 1;
   }
   p.nob = static_cast<int32_t>((a.O + 16 * of - 1) / (16 * of));
+  p.fd_nob = make_div(p.nob);
+  p.fd_g = make_div(a.G);
   const int64_t tiles = (a.N + 16 * rf - 1) / (16 * rf) * p.nob;
   if (tiles > (int64_t(1) << 30)) return hipErrorInvalidConfiguration;
   p.tiles = static_cast<int32_t>(tiles);
