@@ -81,6 +81,7 @@ struct RParams {
   int32_t wt_bytes;   // LDS bytes of the expanded tile: O * C * 2
   int32_t ring_bytes; // LDS bytes of the staged rows: (R + KH - 1) * row_bytes
   int32_t nunits;     // packed 8-column units: (O / G) * K * C / 8
+  Div fd_bpi, fd_dpr, fd_k;
   int32_t rows_a;     // output rows of phase A (its tiles start before the band's later rows land)
 };
 
@@ -156,8 +157,9 @@ __device__ __forceinline__ void resident_body(const RParams& p, uint8_t* lds) {
   const uint32_t id = blockIdx.x;
   const int band = p.grid8 ? static_cast<int>((id % kXcds) * static_cast<uint32_t>(p.grid8) + id / kXcds)
                            : static_cast<int>(id);
-  const int img = band / p.bpi;
-  const int oh0 = (band - img * p.bpi) * p.R;
+  uint32_t brem;
+  const int img = static_cast<int>(divmod(static_cast<uint32_t>(band), p.fd_bpi, brem));
+  const int oh0 = static_cast<int>(brem) * p.R;
   const int rows = min(p.R, p.Ho - oh0);
   const int npix = rows * p.Wo;
   const int nrows = rows + KH - 1;  // staged input rows
@@ -199,8 +201,9 @@ __device__ __forceinline__ void resident_body(const RParams& p, uint8_t* lds) {
   const auto dma_rows = [&](int r0, int r1) {  // returns this wave's instruction count
     int n = 0;
     for (int f = r0 * p.dpr + wave; f < r1 * p.dpr; f += kWaves) {
-      const int r = f / p.dpr;
-      const int j = f - r * p.dpr;
+      uint32_t ju;
+      const int r = static_cast<int>(divmod(static_cast<uint32_t>(f), p.fd_dpr, ju));
+      const int j = static_cast<int>(ju);
       const uint32_t s = static_cast<uint32_t>(j * 64 + lane);
       const uint32_t q = s / CPP;                                  // staged column
       const uint32_t c = (s & (CPP - 1)) ^ ((s >> 4) & (CPP - 1));  // channel chunk held by slot s
@@ -238,11 +241,11 @@ __device__ __forceinline__ void resident_body(const RParams& p, uint8_t* lds) {
   // the format rules out, is clamped into the group), column c0 + e.  A
   // write's LDS bank is set by o % 16 and e; the lanes of a wave hold
   // neighbouring column blocks of one packed row, whose kept rows repeat, so
-  // at step e lane l writes element e ^ (l % 8) of its block instead of e:
+  // at step e lane l writes element e ^ 2 (l % 4) of its block instead of e:
   // one instruction's two-byte stores then spread over four times as many
-  // banks.  (The lane's values and indices are permuted once per unit.)
-  const uint32_t m = static_cast<uint32_t>(lane & 7);
-  const uint32_t bsel = 0x03020100u ^ ((m & 3u) * 0x01010101u);  // byte j <- byte j ^ (m % 4)
+  // banks (the halves of a bank word need no spreading).  (The lane's values
+  // and indices are permuted once per unit.)
+  const uint32_t m = 2u * static_cast<uint32_t>(lane & 3);
 #pragma unroll
   for (int u = 0; u < kUnitsMax; ++u) {
     if (wave_has(u)) {
@@ -250,7 +253,8 @@ __device__ __forceinline__ void resident_body(const RParams& p, uint8_t* lds) {
       if (unit < p.nunits) {
         const int prow = unit / C8;
         const int c0 = (unit - prow * C8) * 8;
-        const int gG = (prow / p.K) * p.G;  // the group's first row
+        uint32_t k;
+        const int gG = static_cast<int>(divmod(static_cast<uint32_t>(prow), p.fd_k, k)) * p.G;  // the group's first row
         const uint32_t ubase = static_cast<uint32_t>((c0 >> 5) * 1024 + ((c0 & 31) >> 3) * 256);
         // element e of (d, ix) below is element e ^ m of the unit
         uint32_t d[4] = {pv[u][0], pv[u][1], pv[u][2], pv[u][3]};
@@ -265,12 +269,8 @@ __device__ __forceinline__ void resident_body(const RParams& p, uint8_t* lds) {
           const uint32_t t0 = d[0], t2 = d[2];
           d[0] = d[1]; d[1] = t0; d[2] = d[3]; d[3] = t2;
         }
-        if (m & 1u) {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) d[j] = __builtin_amdgcn_alignbit(d[j], d[j], 16);
-        }
-        iw[0] = __builtin_amdgcn_perm(iw[0], iw[0], bsel);
-        iw[1] = __builtin_amdgcn_perm(iw[1], iw[1], bsel);
+        iw[0] = __builtin_amdgcn_alignbit(iw[0], iw[0], 8u * (m & 2u));
+        iw[1] = __builtin_amdgcn_alignbit(iw[1], iw[1], 8u * (m & 2u));
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const uint32_t ix = min((iw[e >> 2] >> (8 * (e & 3))) & 0xffu, static_cast<uint32_t>(p.G - 1));
@@ -525,6 +525,9 @@ hipError_t launch_resident(const ProductArgs& a, hipStream_t s) {
   p.ring_bytes = (p.R + g.KH - 1) * p.row_bytes;
   p.nunits = static_cast<int32_t>((a.O / a.G) * a.K * a.C / 8);
   p.rows_a = (p.R + 1) / 2;
+  p.fd_bpi = make_div(p.bpi);
+  p.fd_dpr = make_div(p.dpr);
+  p.fd_k = make_div(a.K);
   const int lds = p.wt_bytes + p.ring_bytes + kEpiBytes;
   const uint32_t grid = static_cast<uint32_t>(bands);
   const bool res = a.residual != nullptr;
