@@ -61,7 +61,8 @@ struct NParams {
   void* Y;
   uint32_t x_bytes, y_bytes;
   int32_t N, C, O, G, K, relu;
-  int32_t H, W, Cin, KW, sh, sw, ph, pw, Ho, Wo;  // convolutions (implicit im2col)
+  int32_t H, W, Cin, KW, sh, sw, ph, pw;  // convolutions (implicit im2col)
+  Div fd_howo, fd_wo;
   int32_t tpw;      // output tiles per slice
   int32_t nslices;  // slices covering the O / 16 (rounded up) output tiles
   int32_t npg;      // pixel groups of 16 P pixels
@@ -133,11 +134,11 @@ __device__ __forceinline__ void narrow_body(const NParams& p, float* sb) {
         }
       } else {
         // output pixel n = (image, oh, ow) -> top-left input position
-        const uint32_t hw = static_cast<uint32_t>(p.Ho * p.Wo);
-        const uint32_t img = n / hw;
-        const uint32_t rem = n - img * hw;
-        const uint32_t oh = rem / static_cast<uint32_t>(p.Wo);
-        const uint32_t ow = rem - oh * static_cast<uint32_t>(p.Wo);
+        // (per lane and group: compiler-made divisions here were a third of the
+        // vector instructions of a group)
+        uint32_t rem, ow;
+        const uint32_t img = divmod(n, p.fd_howo, rem);
+        const uint32_t oh = divmod(rem, p.fd_wo, ow);
         const int ih0 = static_cast<int>(oh) * p.sh - p.ph, iw0 = static_cast<int>(ow) * p.sw - p.pw;
         const bool nok = n < N;
 #pragma unroll
@@ -483,8 +484,8 @@ hipError_t launch_narrow(const ProductArgs& a, hipStream_t s) {
     p.sw = g.sw;
     p.ph = g.ph;
     p.pw = g.pw;
-    p.Ho = g.Ho;
-    p.Wo = g.Wo;
+    p.fd_howo = make_div(static_cast<int64_t>(g.Ho) * g.Wo);
+    p.fd_wo = make_div(g.Wo);
   }
   p.y_bytes = static_cast<uint32_t>(a.N * a.O * (a.y_t == DType::F32 ? 4 : 2));
   p.N = static_cast<int32_t>(a.N);
