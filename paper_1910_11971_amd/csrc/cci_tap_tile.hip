@@ -14,11 +14,15 @@
 //     contiguous bytes each; a tap that falls into the padding reads zero
 //     through the buffer's range check (its offset has bit 31 set);
 //   - the tile is multiplied on v_mfma_f32_16x16x32_bf16.
-// Work split: a workgroup is four waves and owns 128 pixels x 128 outputs;
+// Work split: a team of four waves owns 128 pixels x 128 (or 64) outputs;
 // wave (wp, wo) accumulates pixels 64 wp .. +63 x outputs 64 wo .. +63 in
-// sixteen 16 x 16 accumulators.  A workgroup takes 80 KiB of LDS (three
-// activation buffers, two weight tiles), so two share a CU and the tile
-// builds, barriers and epilogue of one overlap the other's MFMAs.  This
+// sixteen 16 x 16 accumulators.  A team takes 80 KiB of LDS (three activation
+// buffers, two weight tiles), so two share a CU and the tile builds, barriers
+// and epilogue of one overlap the other's MFMAs: two workgroups of one team,
+// or, on small grids, one workgroup whose two teams halve the reduction.
+// Bound by the LDS: a step of two chunks takes ~2 070 cycles, the sum of its
+// fragment reads (128 KiB at ~225 B/clk), zero fill and DMA (32 KiB each at
+// ~60 B/clk) and 64 scatter stores (~5 clk); its MFMAs need 1 024.  This
 // serves the products with long reductions and few output tiles (k x k
 // convolutions over 128-512 channels, 1x1 layers of 10^4 pixels) that leave
 // most CUs idle under 256 x 256 tiles.
