@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "cci_div.hpp"
 #include "cci_types.hpp"
 
 namespace cci {
@@ -38,20 +39,6 @@ template <> struct io<bf16_t> {
     p[i].bits = f32_to_bf16_rne(v);
   }
 };
-
-// Division by a launch constant d: with m = floor(2^32 / d) (all ones for d =
-// 1) the high half of n m is n / d or one less, for every 32-bit n.
-struct Div {
-  uint32_t d, m;
-};
-inline Div make_div(int64_t d) {
-  return Div{static_cast<uint32_t>(d), d > 1 ? static_cast<uint32_t>((uint64_t(1) << 32) / static_cast<uint64_t>(d)) : ~0u};
-}
-__device__ __forceinline__ uint32_t divmod(uint32_t n, const Div v, uint32_t& rem) {
-  const uint32_t q = __umulhi(n, v.m), r = n - q * v.d;
-  rem = r >= v.d ? r - v.d : r;
-  return r >= v.d ? q + 1 : q;
-}
 
 // Fused epilogue operands (device pointers; null = absent).
 template <typename YT>

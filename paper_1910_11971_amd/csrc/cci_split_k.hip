@@ -72,8 +72,8 @@ struct KParams {
   uint32_t x_bytes;
   int32_t H, W, Cin, KH, KW, sh, sw, ph, pw;
   Div fd_howo, fd_wo;
-  uint32_t spt_mul;  // k-step / (Cin / 32) == mulhi(k-step, spt_mul) (Cin == 32: unused)
-  uint32_t kw_mul;   // tap / KW == (tap * kw_mul) >> 16
+  Div fd_spt;       // k-steps of a tap: Cin / 32 (a single tap: all of them)
+  uint32_t kw_mul;  // tap / KW == small_div(tap, kw_mul)
 };
 
 // k-steps whose loads a wave keeps in flight together: as many as fit about
@@ -201,8 +201,9 @@ __global__ __launch_bounds__(kThreads) void split_k_kernel(KParams p) {
       if (s < nks) {
         if constexpr (CONV) {
           // tap and channel block of the k-step
-          const int32_t t = p.Cin == 32 ? s : static_cast<int32_t>(__umulhi(static_cast<uint32_t>(s), p.spt_mul));
-          const int32_t kh = static_cast<int32_t>(static_cast<uint32_t>(t) * p.kw_mul >> 16), kw = t - kh * p.KW;
+          uint32_t in_tap;
+          const int32_t t = static_cast<int32_t>(divmod(static_cast<uint32_t>(s), p.fd_spt, in_tap));
+          const int32_t kh = static_cast<int32_t>(small_div(static_cast<uint32_t>(t), p.kw_mul)), kw = t - kh * p.KW;
           const int32_t c = lane_c0(s) - t * p.Cin;
           const int32_t toff = ((kh * p.W + kw) * p.Cin + c) * 2;
 #pragma unroll
@@ -543,9 +544,8 @@ hipError_t launch_split_k(const ProductArgs& a, hipStream_t s) {
     p.pw = g.pw;
     p.fd_howo = make_div(static_cast<int64_t>(g.Ho) * g.Wo);
     p.fd_wo = make_div(g.Wo);
-    // (a single tap is tap 0 whatever the quotient of its ragged k-steps)
-    p.spt_mul = g.KH * g.KW > 1 ? static_cast<uint32_t>((uint64_t(1) << 32) / static_cast<uint32_t>(g.Cin / 32) + 1) : 0u;
-    p.kw_mul = (1u << 16) / static_cast<uint32_t>(g.KW) + 1;
+    p.fd_spt = make_div(g.KH * g.KW > 1 ? g.Cin / 32 : (g.Cin + 31) / 32);
+    p.kw_mul = make_small_div(g.KW);
   }
   p.nob = static_cast<int32_t>((a.O + 16 * of - 1) / (16 * of));
   p.fd_nob = make_div(p.nob);

@@ -243,6 +243,31 @@ def test_conv_ragged_auto(B, H, W, Cin, O, k, stride, pad, G, K):
              torch.bfloat16, "auto", ep=ep)
 
 
+@pytest.mark.parametrize("KH,KW,Cin,G", [(3, 3, 705184, 8), (5, 5, 424032, 32), (4, 8, 372064, 32)])
+def test_conv_split_k_very_long_taps(KH, KW, Cin, G):
+    """The tap of the last k-step of the last tap: Cin from which a rounded-up reciprocal of Cin / 32 gives the next one."""
+    need_gpu()
+    from paper_1910_11971_amd import cci
+    O = G
+    H, W, pad = KH, KW, (KH // 2, KW // 2)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(Cin)
+    Wt = torch.randn(O, KH * KW * Cin, device=DEV, generator=g)
+    vals, idx = cci.pack(Wt, G, 1, torch.bfloat16)
+    del Wt
+    # only the last 64 channels of a pixel are nonzero: the k-steps in question are most of every sum
+    X = torch.zeros(1, H, W, Cin, device=DEV, dtype=torch.bfloat16)
+    X[..., -64:] = torch.randn(1, H, W, 64, device=DEV, generator=g).bfloat16()
+    Y = cci.conv_im2col(X, vals, idx, G, KH, KW, (1, 1), pad, out_dtype=torch.float32)
+    v = torch.zeros(O, KH * KW * Cin, device=DEV).scatter_(0, idx.long().view(1, -1), vals.float().view(1, -1))
+    v = v.view(O, KH, KW, Cin)[..., -64:].permute(0, 3, 1, 2).double().cpu()
+    x = X[..., -64:].permute(0, 3, 1, 2).double().cpu()
+    ref = torch.nn.functional.conv2d(x, v, padding=pad).permute(0, 2, 3, 1)
+    mag = torch.nn.functional.conv2d(x.abs(), v.abs(), padding=pad).permute(0, 2, 3, 1)
+    # fp32 sums of 64 KH KW nonzero products (bf16 products are exact) in any order
+    assert ((Y.double().cpu() - ref).abs() <= 64 * KH * KW * 2.0 ** -24 * mag).all()
+
+
 def test_conv_tap_tile_refuses_unsupported():
     """Cin % 64 != 0, O % 64 != 0, G = 64, and G = 32 with O % 128 != 0 are refused by the tap-chunk family."""
     need_gpu()
