@@ -277,65 +277,100 @@ struct __attribute__((aligned(sizeof(T) * V))) Cols {
   T v[V];
 };
 
-template <int G, int V, typename XT, typename VT, typename YT>
+// acc += the kept slots of columns c .. c + 3 of one group (slot k of a column
+// at vals / idx + k C) times the columns' activations.  Up to four slots'
+// loads are in flight; slots past K cost nothing (uniform branches).
+template <int G, typename XT, typename VT>
+__device__ __forceinline__ void add_columns4(float (&acc)[G], const XT* X, const VT* vals, const uint8_t* idx, int64_t C,
+                                             int32_t K) {
+  constexpr int KB = 4, V = 4;
+  const Cols<XT, V> xv = *reinterpret_cast<const Cols<XT, V>*>(X);
+  float x[V];
+#pragma unroll
+  for (int v = 0; v < V; ++v) x[v] = io<XT>::load(xv.v, v);
+  for (int32_t k0 = 0; k0 < K; k0 += KB) {
+    Cols<VT, V> pv[KB];
+    Cols<uint8_t, V> pi[KB];
+#pragma unroll
+    for (int k = 0; k < KB; ++k)
+      if (k0 + k < K) {
+        pv[k] = *reinterpret_cast<const Cols<VT, V>*>(vals + (k0 + k) * C);
+        pi[k] = *reinterpret_cast<const Cols<uint8_t, V>*>(idx + (k0 + k) * C);
+      }
+#pragma unroll
+    for (int k = 0; k < KB; ++k)
+      if (k0 + k < K) {
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          const float t = io<VT>::load(pv[k].v, v) * x[v];
+#pragma unroll
+          for (int r = 0; r < G; ++r) acc[r] += pi[k].v[v] == static_cast<uint32_t>(r) ? t : 0.0f;
+        }
+      }
+  }
+}
+
+// Exchange with lane ^ OFF: while more than one row is live, a lane keeps the
+// half of its rows that its bit OFF names and gives the other half away; then
+// the lanes that carry the same row sum it.  Returns the lane's row.
+// (A template and not a loop over `off`: the compiler unrolls a loop's inner
+// one first, its trip count is not yet a constant there, and every access
+// to acc became a select over all rows: 37 KB of code at G = 32.)
+template <int LIVE, int OFF, int G>
+__device__ __forceinline__ int exchange(float (&acc)[G], int lane) {
+  if constexpr (OFF == 0) {
+    return 0;
+  } else if constexpr (LIVE > 1) {
+    constexpr int H = LIVE / 2;
+    const bool up = (lane & OFF) != 0;
+#pragma unroll
+    for (int r = 0; r < H; ++r) {
+      const float give = up ? acc[r] : acc[r + H];
+      const float mine = up ? acc[r + H] : acc[r];
+      acc[r] = mine + __shfl_xor(give, OFF, 64);
+    }
+    return (up ? H : 0) + exchange<H, OFF / 2>(acc, lane);
+  } else {
+    acc[0] += __shfl_xor(acc[0], OFF, 64);
+    return exchange<1, OFF / 2>(acc, lane);
+  }
+}
+
+// VEC: C % 4 == 0 and C > 192.
+template <int G, bool VEC, typename XT, typename VT, typename YT>
 __global__ __launch_bounds__(kThreads) void sparse_mac_rows_kernel(const XT* __restrict__ X, int64_t N, int64_t C,
                                                                    const VT* __restrict__ vals,
                                                                    const uint8_t* __restrict__ idx, int64_t O,
                                                                    int32_t K, Epilogue<YT> ep, YT* __restrict__ Y) {
-  constexpr int KB = 4;  // slots in flight
   const int lane = threadIdx.x & 63;
   const int64_t ngroups = O / G;
   const int64_t wv = static_cast<int64_t>(blockIdx.x) * (kThreads / 64) + (threadIdx.x >> 6);
-  if (wv >= N * ngroups) return;  // whole wave
-  const int64_t n = wv / ngroups, g = wv - n * ngroups;
+  if (wv >= N * ngroups) return;
+  const int64_t n = wv / ngroups, g = wv % ngroups;
   float acc[G];
 #pragma unroll
   for (int r = 0; r < G; ++r) acc[r] = 0.0f;
-  for (int64_t c = V * lane; c < C; c += 64 * V) {
-    const Cols<XT, V> xv = *reinterpret_cast<const Cols<XT, V>*>(X + n * C + c);
-    float x[V];
+  // Columns [0, c4) are taken four a lane, the rest one a lane: a last block
+  // of up to 192 columns costs fewer row compares that way (61 x 264 -> 2488,
+  // G = 8, K = 1: 29.4 us with a second block of four a lane, 15.0 with one).
+  int64_t c4 = 0;
+  if constexpr (VEC) {
+    c4 = C % 256 > 192 ? C : C - C % 256;
+    for (int64_t c = 4 * lane; c < c4; c += 256)
+      add_columns4<G>(acc, X + n * C + c, vals + g * K * C + c, idx + g * K * C + c, C, K);
+  }
+  for (int64_t c = c4 + lane; c < C; c += 64) {
+    const float x = io<XT>::load(X, n * C + c);
+#pragma unroll 4
+    for (int32_t k = 0; k < K; ++k) {
+      const int64_t q = (g * K + k) * C + c;
+      const uint32_t i = idx[q];
+      const float v = io<VT>::load(vals, q) * x;
 #pragma unroll
-    for (int v = 0; v < V; ++v) x[v] = io<XT>::load(xv.v, v);
-    for (int32_t k0 = 0; k0 < K; k0 += KB) {
-      Cols<VT, V> pv[KB];
-      Cols<uint8_t, V> pi[KB];
-#pragma unroll
-      for (int k = 0; k < KB; ++k) {
-        const int64_t q = (g * K + (k0 + k < K ? k0 + k : K - 1)) * C + c;
-        pv[k] = *reinterpret_cast<const Cols<VT, V>*>(vals + q);
-        pi[k] = *reinterpret_cast<const Cols<uint8_t, V>*>(idx + q);
-      }
-#pragma unroll
-      for (int k = 0; k < KB; ++k)
-#pragma unroll
-        for (int v = 0; v < V; ++v) {
-          const uint32_t i = k0 + k < K ? pi[k].v[v] : 0xffffu;  // (no row: never matches)
-          const float t = io<VT>::load(pv[k].v, v) * x[v];
-#pragma unroll
-          for (int r = 0; r < G; ++r) acc[r] += i == static_cast<uint32_t>(r) ? t : 0.0f;
-        }
+      for (int r = 0; r < G; ++r) acc[r] += i == static_cast<uint32_t>(r) ? v : 0.0f;
     }
   }
-  // Exchange with lane ^ off: while more than one row is left, a lane keeps
-  // the half of its rows that its bit `off` names and gives the other half
-  // away; then the lanes that carry the same row sum it.
-  int row = 0;
-#pragma unroll
-  for (int off = 32, live = G; off > 0; off >>= 1) {
-    if (live > 1) {
-      live >>= 1;
-      const bool up = (lane & off) != 0;
-#pragma unroll
-      for (int r = 0; r < live; ++r) {
-        const float give = up ? acc[r] : acc[r + live];
-        const float mine = up ? acc[r + live] : acc[r];
-        acc[r] = mine + __shfl_xor(give, off, 64);
-      }
-      row += up ? live : 0;
-    } else {
-      acc[0] += __shfl_xor(acc[0], off, 64);
-    }
-  }
+  const int row = exchange<G, 32>(acc, lane);
   // one lane per row: those whose bits below the exchanged ones are zero
   if ((lane & (64 / G - 1)) == 0) {
     const int64_t o = g * G + row;
@@ -350,12 +385,12 @@ void launch_rows_g(const ProductArgs& a, const Epilogue<YT>& ep, hipStream_t s) 
   const auto X = static_cast<const XT*>(a.X);
   const auto V = static_cast<const VT*>(a.vals);
   const auto Y = static_cast<YT*>(a.Y);
-  if (a.C % 4 == 0)
-    hipLaunchKernelGGL((sparse_mac_rows_kernel<G, 4, XT, VT, YT>), grid, dim3(kThreads), 0, s, X, a.N, a.C, V, a.idx, a.O,
-                       a.K, ep, Y);
+  if (a.C % 4 == 0 && a.C > 192)
+    hipLaunchKernelGGL((sparse_mac_rows_kernel<G, true, XT, VT, YT>), grid, dim3(kThreads), 0, s, X, a.N, a.C, V, a.idx,
+                       a.O, a.K, ep, Y);
   else
-    hipLaunchKernelGGL((sparse_mac_rows_kernel<G, 1, XT, VT, YT>), grid, dim3(kThreads), 0, s, X, a.N, a.C, V, a.idx, a.O,
-                       a.K, ep, Y);
+    hipLaunchKernelGGL((sparse_mac_rows_kernel<G, false, XT, VT, YT>), grid, dim3(kThreads), 0, s, X, a.N, a.C, V, a.idx,
+                       a.O, a.K, ep, Y);
 }
 
 template <typename XT, typename VT, typename YT>

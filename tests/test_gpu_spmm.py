@@ -370,7 +370,10 @@ def test_spmm_auto_still_refuses(N, C, O, G, K):
 
 
 @pytest.mark.parametrize("N,C,O,G,K", [(3, 260, 32, 16, 5), (9, 64, 64, 32, 31), (2, 1024, 8, 2, 1), (255, 20, 16, 4, 4),
-                                       (7, 259, 40, 8, 3), (1, 8, 64, 32, 2)])
+                                       (7, 259, 40, 8, 3), (1, 8, 64, 32, 2),
+                                       # last blocks of 0, 192 (one column a lane), 196 and 252 columns (four a lane)
+                                       (5, 512, 96, 32, 1), (2, 448, 64, 2, 2), (4, 196, 32, 16, 3), (6, 508, 24, 4, 1),
+                                       (130, 773, 64, 8, 6)])
 def test_spmm_fp32_few_rows(N, C, O, G, K):
     """Vector-ALU kernel of few rows: four columns a lane and one, every row exchange, slot remainders."""
     need_gpu()
