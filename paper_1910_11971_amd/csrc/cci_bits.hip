@@ -78,39 +78,61 @@ struct FParams {
   int32_t N, C, O, G, K, b, relu;
 };
 
-constexpr int kCW = 128;                 // columns of a chunk
-constexpr int kTileB = 16 * kCW * 2;     // bytes of a wave's tile
+// ReLU, rounding and store of a lane's four outputs.
+template <typename YT>
+__device__ __forceinline__ void store4(const FParams& p, float (&y)[4], int64_t yo) {
+  if (p.relu) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) y[r] = y[r] > 0.0f ? y[r] : (y[r] != y[r] ? y[r] : 0.0f);
+  }
+  if (std::is_same<YT, float>::value) {
+    *reinterpret_cast<f32x4_t*>(static_cast<float*>(p.Y) + yo) = f32x4_t{y[0], y[1], y[2], y[3]};
+  } else {
+    *reinterpret_cast<u16x4_t*>(static_cast<uint16_t*>(p.Y) + yo) =
+        u16x4_t{f32_to_bf16_rne(y[0]), f32_to_bf16_rne(y[1]), f32_to_bf16_rne(y[2]), f32_to_bf16_rne(y[3])};
+  }
+}
+
+// Columns of a chunk.  PAIR: two workgroups share a CU, with half of the
+// registers and so half of the columns each.
+constexpr int chunk_cols(bool pair) { return pair ? 64 : 128; }
+constexpr int tile_bytes(bool pair) { return 16 * chunk_cols(pair) * 2; }  // a wave's tile
+// Packed rows that a wave's lanes read at once (one 8-column unit per lane).
+constexpr int unit_rows(bool pair) { return 64 * 8 / chunk_cols(pair); }
 
 // Loads of one chunk: up to PL packed units per lane (values and index
 // words) and the lane's X fragments.
-template <int PL, int NB>
+template <int PL, int NB, int STEPS>
 struct Fetch {
   u32x4_t v[PL];
   uint32_t ix[PL][3];
-  u32x4_t x[4][NB];
+  u32x4_t x[STEPS][NB];
 };
 
-// Chunks in flight per wave: as many as fit about 170 registers, at most 4.
-constexpr int depth(int pl, int nb) {
-  const int d = 170 / (pl * 7 + nb * 16);
+// Chunks in flight per wave: as many as fit about 170 (PAIR: 64) registers,
+// at most 4.
+constexpr int depth(int pl, int nb, bool pair) {
+  const int d = (pair ? 64 : 170) / (pl * 7 + nb * chunk_cols(pair) / 8);
   return d < 1 ? 1 : d > 4 ? 4 : d;
 }
 
 // PL: packed units per lane and pass; ONE: one pass covers a chunk (else the
 // units of a chunk are walked in passes, loaded inline).
-template <int NB, int PL, bool ONE, typename YT>
-__global__ __launch_bounds__(kFThreads) void spmm_bits_kernel(FParams p) {
-  constexpr int D = ONE ? depth(PL, NB) : 1;
-  __shared__ __attribute__((aligned(16))) uint8_t tiles[kFWaves][kTileB];
-  __shared__ __attribute__((aligned(16))) f32x4_t red[kFWaves][NB][64];
+template <int NB, int PL, bool ONE, bool PAIR, typename YT>
+__global__ __launch_bounds__(kFThreads, PAIR ? 4 : 2) void spmm_bits_kernel(FParams p) {
+  constexpr int D = ONE ? depth(PL, NB, PAIR) : 1;
+  constexpr int CW = chunk_cols(PAIR), UN = CW / 8, RP = unit_rows(PAIR), STEPS = CW / 32;
+  // a wave's weight tile, later its partial sums ([NB][64] f32x4_t)
+  constexpr int kTile = tile_bytes(PAIR), kSums = NB * 64 * static_cast<int>(sizeof(f32x4_t));
+  __shared__ __attribute__((aligned(16))) uint8_t tiles[kFWaves][kTile > kSums ? kTile : kSums];
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int32_t o0 = static_cast<int32_t>(blockIdx.x) * 16;
   const int32_t g_lo = o0 / p.G, g_hi = min((o0 + 15) / p.G, p.O / p.G - 1);
-  // packed rows (group, slot) x 16 units of a chunk: lane & 15 is the unit
-  // (8 columns), entry u of a lane packed row lane / 16 + 4 u
+  // packed rows (group, slot) x UN units of a chunk: lane % UN is the unit (8
+  // columns), entry u of a lane packed row lane / UN + RP u
   const int32_t nrows = (g_hi - g_lo + 1) * p.K;
-  const int32_t c8 = lane & 15, r4 = lane >> 4;
+  const int32_t c8 = lane % UN, r0l = lane / UN;
   const bool full = p.K == p.G;
 
   const __amdgpu_buffer_rsrc_t xr =
@@ -163,7 +185,7 @@ __global__ __launch_bounds__(kFThreads) void spmm_bits_kernel(FParams p) {
     if (full) {
       const int32_t row = row0 + r - gl * p.K;
       if (r < nrows && row >= 0 && row < 16)
-        *reinterpret_cast<u32x4_t*>(tile + row * 256 + ((c8 ^ row) * 16)) = v;
+        *reinterpret_cast<u32x4_t*>(tile + row * (2 * CW) + ((c8 ^ (row % UN)) * 16)) = v;
       return;
     }
     const uint32_t sh = static_cast<uint32_t>((e * p.b) & 31);
@@ -175,7 +197,7 @@ __global__ __launch_bounds__(kFThreads) void spmm_bits_kernel(FParams p) {
       for (int t = 0; t < 8; ++t) {
         const int32_t row = row0 + static_cast<int32_t>(static_cast<uint32_t>(bits >> (t * p.b)) & mask);
         if (row >= 0 && row < 16)
-          *reinterpret_cast<uint16_t*>(tile + row * 256 + ((c8 ^ row) * 16) + 2 * t) =
+          *reinterpret_cast<uint16_t*>(tile + row * (2 * CW) + ((c8 ^ (row % UN)) * 16) + 2 * t) =
               static_cast<uint16_t>(v[t >> 1] >> (16 * (t & 1)));
       }
     }
@@ -183,21 +205,21 @@ __global__ __launch_bounds__(kFThreads) void spmm_bits_kernel(FParams p) {
   auto clear = [&]() {
     if (full) return;
 #pragma unroll
-    for (int q = 0; q < kTileB / 1024; ++q)
+    for (int q = 0; q < kTile / 1024; ++q)
       *reinterpret_cast<u32x4_t*>(tile + q * 1024 + lane * 16) = u32x4_t{0u, 0u, 0u, 0u};
   };
 
-  auto fetch = [&](int32_t ch, Fetch<PL, NB>& f) {
-    const int32_t c0 = ch * kCW;
+  auto fetch = [&](int32_t ch, Fetch<PL, NB, STEPS>& f) {
+    const int32_t c0 = ch * CW;
     if constexpr (ONE) {
 #pragma unroll
       for (int u = 0; u < PL; ++u) {
-        const int32_t r = r4 + 4 * u;
+        const int32_t r = r0l + RP * u;
         load_unit(unit_e(r) + c0, r < nrows && c0 + 8 * c8 < p.C, f.v[u], f.ix[u]);
       }
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < STEPS; ++j)
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
         const uint32_t n = static_cast<uint32_t>(16 * nb + ti);
@@ -213,8 +235,8 @@ __global__ __launch_bounds__(kFThreads) void spmm_bits_kernel(FParams p) {
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) acc[nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  const int32_t nch = (p.C + kCW - 1) / kCW;
-  Fetch<PL, NB> st[D];
+  const int32_t nch = (p.C + CW - 1) / CW;
+  Fetch<PL, NB, STEPS> st[D];
 #pragma unroll
   for (int d = 0; d < D; ++d)
     if (w + kFWaves * d < nch) fetch(w + kFWaves * d, st[d]);
@@ -223,30 +245,30 @@ __global__ __launch_bounds__(kFThreads) void spmm_bits_kernel(FParams p) {
     for (int d = 0; d < D; ++d) {
       const int32_t ch = base + kFWaves * d;
       if (ch < nch) {
-        const int32_t c0 = ch * kCW;
+        const int32_t c0 = ch * CW;
         clear();
         if constexpr (ONE) {
 #pragma unroll
-          for (int u = 0; u < PL; ++u) scatter(r4 + 4 * u, unit_e(r4 + 4 * u) + c0, st[d].v[u], st[d].ix[u]);
+          for (int u = 0; u < PL; ++u) scatter(r0l + RP * u, unit_e(r0l + RP * u) + c0, st[d].v[u], st[d].ix[u]);
         } else {
 #pragma unroll 1
-          for (int32_t r0 = 0; r0 < nrows; r0 += 4 * PL) {
+          for (int32_t r0 = 0; r0 < nrows; r0 += RP * PL) {
 #pragma unroll
             for (int u = 0; u < PL; ++u) {
-              const int32_t r = r0 + r4 + 4 * u;
+              const int32_t r = r0 + r0l + RP * u;
               load_unit(unit_e(r) + c0, r < nrows && c0 + 8 * c8 < p.C, st[d].v[u], st[d].ix[u]);
             }
 #pragma unroll
             for (int u = 0; u < PL; ++u) {
-              const int32_t r = r0 + r4 + 4 * u;
+              const int32_t r = r0 + r0l + RP * u;
               scatter(r, unit_e(r) + c0, st[d].v[u], st[d].ix[u]);
             }
           }
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < STEPS; ++j) {
           const bf16x8_t a =
-              *reinterpret_cast<const bf16x8_t*>(tile + ti * 256 + (((4 * j + tq) ^ ti) * 16));
+              *reinterpret_cast<const bf16x8_t*>(tile + ti * (2 * CW) + (((4 * j + tq) ^ (ti % UN)) * 16));
 #pragma unroll
           for (int nb = 0; nb < NB; ++nb)
             acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8_t, st[d].x[j][nb]), acc[nb],
@@ -259,49 +281,199 @@ __global__ __launch_bounds__(kFThreads) void spmm_bits_kernel(FParams p) {
 
   // ---- sum the eight waves' partials; wave nb finishes X rows 16 nb .. +16
 #pragma unroll
+  for (int nb = 0; nb < NB; ++nb) reinterpret_cast<f32x4_t*>(tile)[nb * 64 + lane] = acc[nb];
+  __syncthreads();
+  if (w >= NB) return;
+  const auto part = [&](int v) { return reinterpret_cast<const f32x4_t*>(tiles[v])[w * 64 + lane]; };
+  f32x4_t sum = part(0);
+#pragma unroll
+  for (int v = 1; v < kFWaves; ++v) sum += part(v);
+  if (!eok) return;
+  float y[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) y[r] = sum[r] * sc[r] + bi[r] + rs[r];
+  store4<YT>(p, y, yo);
+}
+
+// The same product in k-steps of 32 columns, one in flight per wave: a lane
+// takes one column of a packed row, so few packed rows (step_rows below)
+// still occupy all of them, and 42-80 registers and 16-40 KiB of LDS let up
+// to four workgroups share a CU.
+// Loads of one k-step: up to PL kept entries per lane (index word(s) and
+// value) and the lane's X fragments.
+template <int PL, int NB>
+struct StepFetch {
+  uint32_t lo[PL], hi[PL];
+  uint16_t v[PL];
+  u32x4_t x[NB];
+};
+
+template <int NB, int PL, typename YT>
+__global__ __launch_bounds__(kFThreads) void few_step_kernel(FParams p) {
+  __shared__ __attribute__((aligned(16))) uint8_t tiles[kFWaves][1024];
+  __shared__ __attribute__((aligned(16))) f32x4_t red[kFWaves][NB][64];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int32_t o0 = static_cast<int32_t>(blockIdx.x) * 16;
+  const int32_t g_lo = o0 / p.G, g_hi = min((o0 + 15) / p.G, p.O / p.G - 1);
+  // (group, slot) pairs cover the k-step's 32 columns: lanes 0..31 take the
+  // even pairs, lanes 32..63 the odd ones, lane & 31 the column; entry u of
+  // a lane is pair pk + 2u, at packed offset base[u] + 32 s in k-step s
+  const int32_t npairs = (g_hi - g_lo + 1) * p.K;
+  const int32_t pk = lane >> 5, cj = lane & 31;
+  int64_t base[PL];
+  int32_t row0[PL];
+  bool on[PL];
+#pragma unroll
+  for (int u = 0; u < PL; ++u) {
+    const int32_t q = pk + 2 * u;
+    on[u] = q < npairs;
+    const int32_t gl = on[u] ? q / p.K : 0, k = on[u] ? q - gl * p.K : 0;
+    base[u] = (static_cast<int64_t>(g_lo + gl) * p.K + k) * p.C + cj;
+    row0[u] = (g_lo + gl) * p.G - o0;
+  }
+
+  const __amdgpu_buffer_rsrc_t xr =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.X), (short)0, static_cast<int>(p.x_bytes), kRsrcWord3);
+  const __amdgpu_buffer_rsrc_t ir =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.idx), (short)0, static_cast<int>(p.i_bytes), kRsrcWord3);
+  const __amdgpu_buffer_rsrc_t vr =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.vals), (short)0, static_cast<int>(p.v_bytes), kRsrcWord3);
+  const uint32_t mask = (1u << p.b) - 1u;
+  uint8_t* tile = tiles[w];
+  const int ti = lane & 15, tq = lane >> 4;
+  const uint8_t* frag = tile + ti * 64 + ((tq ^ ((ti >> 2) & 3)) * 16);
+
+  auto fetch = [&](int32_t s, StepFetch<PL, NB>& f) {
+    const int32_t c0 = s * 32;
+#pragma unroll
+    for (int u = 0; u < PL; ++u) {
+      const int64_t e = base[u] + c0;
+      const uint32_t voff = on[u] ? static_cast<uint32_t>(e) * 2u : 0x80000000u;
+      f.v[u] = __builtin_amdgcn_raw_buffer_load_b16(vr, voff, 0, 0);
+      if (p.b == 8) {
+        f.lo[u] = __builtin_amdgcn_raw_buffer_load_b8(ir, on[u] ? static_cast<uint32_t>(e) : 0x80000000u, 0, 0);
+        f.hi[u] = 0;
+      } else {
+        const uint32_t off = on[u] ? static_cast<uint32_t>((e * p.b) >> 5) * 4u : 0x80000000u;
+        f.lo[u] = __builtin_amdgcn_raw_buffer_load_b32(ir, off, 0, 0);
+        f.hi[u] = __builtin_amdgcn_raw_buffer_load_b32(ir, on[u] ? off + 4u : 0x80000000u, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      const uint32_t n = static_cast<uint32_t>(16 * nb + ti);
+      const uint32_t off = n < static_cast<uint32_t>(p.N)
+                               ? (n * static_cast<uint32_t>(p.C) + static_cast<uint32_t>(c0 + 8 * tq)) * 2u
+                               : 0x80000000u;
+      f.x[nb] = __builtin_amdgcn_raw_buffer_load_b128(xr, off, 0, 0);
+    }
+  };
+
+  f32x4_t acc[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) acc[nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  const int32_t nks = p.C / 32;
+  StepFetch<PL, NB> cur, nxt;
+  if (w < nks) fetch(w, cur);
+  for (int32_t s = w; s < nks; s += kFWaves) {
+    if (s + kFWaves < nks) fetch(s + kFWaves, nxt);
+    const int32_t c0 = s * 32;
+    *reinterpret_cast<u32x4_t*>(tile + lane * 16) = u32x4_t{0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int u = 0; u < PL; ++u) {
+      const int64_t e = base[u] + c0;
+      const uint32_t r = p.b == 8 ? cur.lo[u] : __builtin_amdgcn_alignbit(cur.hi[u], cur.lo[u],
+                                                                          static_cast<uint32_t>((e * p.b) & 31)) & mask;
+      const int32_t row = row0[u] + static_cast<int32_t>(r);
+      if (on[u] && row >= 0 && row < 16)
+        *reinterpret_cast<uint16_t*>(tile + row * 64 + (((cj >> 3) ^ ((row >> 2) & 3)) * 16) + (cj & 7) * 2) = cur.v[u];
+    }
+    const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(frag);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+      acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8_t, cur.x[nb]), acc[nb], 0, 0, 0);
+    cur = nxt;
+  }
+
+  // ---- sum the eight waves' partials; wave nb finishes X rows 16 nb .. +16
+#pragma unroll
   for (int nb = 0; nb < NB; ++nb) red[w][nb][lane] = acc[nb];
   __syncthreads();
   if (w >= NB) return;
   f32x4_t sum = red[0][w][lane];
 #pragma unroll
   for (int v = 1; v < kFWaves; ++v) sum += red[v][w][lane];
-  if (!eok) return;
+  const int32_t n = 16 * w + ti;
+  const int32_t o = o0 + 4 * tq;  // lane holds outputs o .. o+3 of row n
+  if (n >= p.N || o >= p.O) return;  // (O % 4 == 0: a lane's 4 outputs are all inside or all past O)
+  const bool yf32 = std::is_same<YT, float>::value;
+  const int64_t yo = static_cast<int64_t>(n) * p.O + o;
   float y[4];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) y[r] = sum[r] * sc[r] + bi[r] + rs[r];
-  if (p.relu) {
+  for (int r = 0; r < 4; ++r) {
+    y[r] = sum[r];
+    if (p.scale) y[r] *= p.scale[o + r];
+    if (p.bias) y[r] += p.bias[o + r];
+  }
+  if (p.residual) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) y[r] = y[r] > 0.0f ? y[r] : (y[r] != y[r] ? y[r] : 0.0f);
+    for (int r = 0; r < 4; ++r)
+      y[r] += yf32 ? static_cast<const float*>(p.residual)[yo + r]
+                   : bf16_to_f32(static_cast<const uint16_t*>(p.residual)[yo + r]);
   }
-  if (yf32) {
-    *reinterpret_cast<f32x4_t*>(static_cast<float*>(p.Y) + yo) = f32x4_t{y[0], y[1], y[2], y[3]};
-  } else {
-    *reinterpret_cast<u16x4_t*>(static_cast<uint16_t*>(p.Y) + yo) =
-        u16x4_t{f32_to_bf16_rne(y[0]), f32_to_bf16_rne(y[1]), f32_to_bf16_rne(y[2]), f32_to_bf16_rne(y[3])};
-  }
+  store4<YT>(p, y, yo);
 }
 
-template <int NB, int PL, bool ONE>
+template <int NB, int PL, bool ONE, bool PAIR>
 hipError_t launch_fp(const FParams& p, DType y_t, hipStream_t s) {
   const dim3 grid(static_cast<uint32_t>((p.O + 15) / 16));
   if (y_t == DType::F32)
-    hipLaunchKernelGGL((spmm_bits_kernel<NB, PL, ONE, float>), grid, dim3(kFThreads), 0, s, p);
+    hipLaunchKernelGGL((spmm_bits_kernel<NB, PL, ONE, PAIR, float>), grid, dim3(kFThreads), 0, s, p);
   else
-    hipLaunchKernelGGL((spmm_bits_kernel<NB, PL, ONE, bf16_t>), grid, dim3(kFThreads), 0, s, p);
+    hipLaunchKernelGGL((spmm_bits_kernel<NB, PL, ONE, PAIR, bf16_t>), grid, dim3(kFThreads), 0, s, p);
   return hipGetLastError();
 }
 
-// PL: packed units a lane reads per chunk, a quarter of the packed rows of
-// the groups that 16 consecutive outputs starting at a multiple of 16 can
-// touch.  Up to 4 they are loaded chunks ahead; beyond, the walk in passes.
-template <int NB>
+// Groups that 16 consecutive outputs starting at a multiple of 16 can touch.
+int32_t tile_groups(int32_t G) { return 16 % G == 0 ? 16 / G : (G % 16 == 0 ? 1 : 15 / G + 2); }
+
+// PL: packed units a lane reads per chunk: the packed rows of those groups,
+// spread over the lanes.  Up to 4 they are loaded chunks ahead; beyond, the walk in
+// passes.
+template <int NB, bool PAIR>
 hipError_t launch_f(const FParams& p, DType y_t, hipStream_t s) {
-  const int32_t groups = 16 % p.G == 0 ? 16 / p.G : (p.G % 16 == 0 ? 1 : 15 / p.G + 2);
-  const int32_t pl = (groups * p.K + 3) / 4;
-  if (pl <= 1) return launch_fp<NB, 1, true>(p, y_t, s);
-  if (pl <= 2) return launch_fp<NB, 2, true>(p, y_t, s);
-  if (pl <= 4) return launch_fp<NB, 4, true>(p, y_t, s);
-  return launch_fp<NB, 4, false>(p, y_t, s);
+  const int32_t pl = (tile_groups(p.G) * p.K + unit_rows(PAIR) - 1) / unit_rows(PAIR);
+  if (pl <= 1) return launch_fp<NB, 1, true, PAIR>(p, y_t, s);
+  if (pl <= 2) return launch_fp<NB, 2, true, PAIR>(p, y_t, s);
+  if (!PAIR && pl <= 4) return launch_fp<NB, 4, true, false>(p, y_t, s);
+  return launch_fp<NB, PAIR ? 2 : 4, false, PAIR>(p, y_t, s);
+}
+
+// PL: kept entries a lane reads per k-step, half of the packed rows.
+template <int NB>
+hipError_t launch_step(const FParams& p, int32_t rows, DType y_t, hipStream_t s) {
+  const dim3 grid(static_cast<uint32_t>((p.O + 15) / 16));
+  const auto launch = [&](auto pl) {
+    constexpr int PL = decltype(pl)::value;
+    if (y_t == DType::F32)
+      hipLaunchKernelGGL((few_step_kernel<NB, PL, float>), grid, dim3(kFThreads), 0, s, p);
+    else
+      hipLaunchKernelGGL((few_step_kernel<NB, PL, bf16_t>), grid, dim3(kFThreads), 0, s, p);
+    return hipGetLastError();
+  };
+  if (rows <= 2) return launch(std::integral_constant<int, 1>{});
+  if (rows <= 4) return launch(std::integral_constant<int, 2>{});
+  return launch(std::integral_constant<int, 3>{});
+}
+
+template <bool PAIR>
+hipError_t launch_n(const FParams& p, DType y_t, hipStream_t s) {
+  if (p.N <= 16) return launch_f<1, PAIR>(p, y_t, s);
+  if (p.N <= 32) return launch_f<2, PAIR>(p, y_t, s);
+  if (p.N <= 48) return launch_f<3, PAIR>(p, y_t, s);
+  return launch_f<4, PAIR>(p, y_t, s);
 }
 
 }  // namespace
@@ -342,10 +514,14 @@ hipError_t launch_spmm_bits(const void* X, int64_t N, int64_t C, const void* val
   p.K = K;
   p.b = b;
   p.relu = relu;
-  if (N <= 16) return launch_f<1>(p, y_t, s);
-  if (N <= 32) return launch_f<2>(p, y_t, s);
-  if (N <= 48) return launch_f<3>(p, y_t, s);
-  return launch_f<4>(p, y_t, s);
+  const int32_t rows = tile_groups(G) * K;
+  const bool many = O > 16 * 256;
+  if (rows <= 2 || (rows <= 4 && (many || C < 256)) || (rows <= 6 && C < 128 && O > 16 * 512)) {
+    if (N <= 16) return launch_step<1>(p, rows, y_t, s);
+    if (N <= 32) return launch_step<2>(p, rows, y_t, s);
+    return launch_step<4>(p, rows, y_t, s);
+  }
+  return many || C <= 1024 ? launch_n<true>(p, y_t, s) : launch_n<false>(p, y_t, s);
 }
 
 }  // namespace cci

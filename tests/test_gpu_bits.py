@@ -94,6 +94,12 @@ def test_spmm_bits_fc4096_every_output(N, K):
     # every index width of the units: 1, 3, 5, 6, 7 bits; packed rows beyond one pass
     (7, 416, 32, 2, 1), (20, 352, 40, 5, 3), (3, 160, 64, 32, 3), (5, 288, 64, 64, 40), (40, 224, 128, 128, 70),
     (12, 192, 36, 9, 4),
+    # 32-column steps (few packed rows): two, four and six rows, 16, 32 and 64 row tiles, steps without a wave's share
+    (50, 352, 32, 16, 2), (9, 224, 4112, 16, 3), (33, 96, 8208, 8, 3), (16, 64, 40, 4, 1), (20, 2080, 32, 32, 2),
+    # 64-column chunks (two workgroups a CU): one and two units a lane, whole units, passes, half a last chunk
+    (17, 1056, 4112, 8, 4), (64, 160, 48, 8, 8), (1, 96, 36, 9, 5), (33, 992, 64, 32, 20), (48, 1024, 128, 128, 70),
+    # 128-column chunks in passes
+    (3, 1184, 64, 64, 40),
 ])
 def test_spmm_bits_chunks(N, C, O, G, K):
     need_gpu()
