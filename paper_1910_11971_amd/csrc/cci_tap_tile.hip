@@ -37,6 +37,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "cci_chunks.hpp"
 #include "cci_device.hpp"
 #include "cci_launch.hpp"
 
@@ -192,7 +193,7 @@ __device__ __forceinline__ void tap_tile_body(const TParams& p, uint8_t* const l
   uint8_t* const lds = lds0 + team * lds_bytes(TO);
   // this team's chunks: nch from chunk ch0 on (both teams run the same number
   // of steps; a chunk past the reduction is all zeros)
-  const int nch = (p.nch + KS - 1) / KS, ch0 = team * nch;
+  const int nch = team_chunks(p.nch, KS), ch0 = team * nch;
 
   // ---- tile of this workgroup ---------------------------------------------
   // Dispatch places workgroup b on XCD b % 8; L numbers the workgroups of one
@@ -338,10 +339,11 @@ __device__ __forceinline__ void tap_tile_body(const TParams& p, uint8_t* const l
         for (int u = 0; u < UPL; ++u) voff[u] = ioff[u] = kOOB;
       }
     }
+    const uint32_t at = static_cast<uint32_t>(decltype(tail)::value ? load_chunk(ch0 + ch, p.nch) : ch0 + ch);
 #pragma unroll
     for (int u = 0; u < UPL; ++u) {
-      pv[k][u] = load_x4(vd, voff[u], static_cast<uint32_t>(ch0 + ch) * (kCK * 2));
-      if constexpr (!FULL) pi[k][u] = load_x2(id, ioff[u], static_cast<uint32_t>(ch0 + ch) * kCK);
+      pv[k][u] = load_x4(vd, voff[u], at * (kCK * 2));
+      if constexpr (!FULL) pi[k][u] = load_x2(id, ioff[u], at * kCK);
     }
   };
   auto w_fence = [&](auto kc) { fence_stage<decltype(kc)::value, FULL>(pv, pi); };

@@ -136,6 +136,14 @@ def test_spmm_bf16_ragged_auto(N, C, O, G, K):
     run_case(rand_x(N, C, torch.bfloat16, N + C), rand_w(O, C, O + G), G, K, torch.float32, "auto")
 
 
+@pytest.mark.parametrize("N,C,O,G", [(20000, 264, 8, 8), (17000, 776, 16, 16), (20000, 272, 8, 4)])
+def test_spmm_ragged_single_packed_row(N, C, O, G):
+    """One or two packed rows and a second team whose last chunk is empty: its uniform offset would be past them."""
+    need_gpu()
+    rows = np.unique(np.concatenate([np.arange(0, 256), np.arange(N - 200, N), np.arange(0, N, 97)]))
+    run_case(rand_x(N, C, torch.bfloat16, N + C), rand_w(O, C, O + G), G, 1, torch.float32, "auto", rows=rows)
+
+
 @pytest.mark.parametrize("N,C,O", [(3000, 136, 136), (130, 72, 48)])  # tap-chunk, split-reduction
 def test_spmm_ragged_reduction_keeps_neighbours_out(N, C, O):
     """The columns past a ragged reduction are another packed row's (here all infinite) and X's next row: neither may

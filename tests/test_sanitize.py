@@ -49,10 +49,11 @@ def test_abi_host_layer_under_sanitizers(build_dir):
 
 
 @pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir("/opt/rocm/include"), reason="needs g++ and HIP headers")
-def test_launch_constant_divisions(build_dir):
-    exe = os.path.join(build_dir, "div_driver")
+@pytest.mark.parametrize("name", ["div", "chunk"])
+def test_launch_constant_arithmetic(build_dir, name):
+    exe = os.path.join(build_dir, f"{name}_driver")
     _run(["g++", "-O2", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include",
-          os.path.join(HERE, "sanitize", "div_driver.cpp"), "-L/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib",
-          "-o", exe], build_dir)
+          os.path.join(HERE, "sanitize", f"{name}_driver.cpp"), "-L/opt/rocm/lib", "-lamdhip64",
+          "-Wl,-rpath,/opt/rocm/lib", "-o", exe], build_dir)
     r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
-    assert r.returncode == 0 and "div driver ok" in r.stdout, r.stdout + r.stderr
+    assert r.returncode == 0 and f"{name} driver ok" in r.stdout, r.stdout + r.stderr
