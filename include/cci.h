@@ -188,7 +188,13 @@ cci_status cci_pack(const float *W, int64_t O, int64_t C, int32_t G,
  * X: device [N][C] of x_t.  vals/idx as produced by cci_pack.  Y: device
  * [N][O] of y_t.  Supported (x_t, val_t, y_t): (F32, F32, F32) and
  * (BF16, BF16, BF16 or F32); anything else is CCI_EUNSUPPORTED.  The kernel
- * family is the library's choice (CCI_ALGO_AUTO). */
+ * family is the library's choice (CCI_ALGO_AUTO).
+ * An infinity or NaN in X[n][c] reaches the outputs of row n that keep
+ * column c.  On the bf16 families, which multiply the dropped weights as
+ * zeros, it makes every output of row n NaN; not on CCI_ALGO_SPARSE_MAC, nor
+ * under CCI_ALGO_AUTO where the split-reduction or tap-chunk kernels take a
+ * product that would otherwise run on CCI_ALGO_SPARSE_MAC (for instance
+ * C % 32 != 0 over more than 256 columns).  Other rows see none of it. */
 cci_status cci_spmm(const void *X, cci_dtype x_t, int64_t N, int64_t C,
                     const void *vals, cci_dtype val_t, const uint8_t *idx,
                     int64_t O, int32_t G, int32_t K, const cci_epilogue *ep,

@@ -89,10 +89,14 @@ bool few_rows_ok(const cci::ProductArgs& a) {
 // being refused.
 cci_algo ragged_route(cci::ProductArgs& a, cci_algo chosen, bool mac_next) {
   a.ragged = true;
+  // (The one taken from the sparse-MAC kernels keeps their treatment of
+  // infinities and NaN in X.)
   const auto accepted = [&] {
-    if (chosen == CCI_ALGO_SPARSE_MAC) return cci::sparse_mac_supports(a);
-    if (chosen == CCI_ALGO_DENSE_TILE_MFMA)
-      return (mac_next && cci::sparse_mac_supports(a)) || cci::dense_tile_supports(a);
+    const bool mac = chosen == CCI_ALGO_SPARSE_MAC ||
+                     (chosen == CCI_ALGO_DENSE_TILE_MFMA && mac_next && !cci::dense_tile_supports(a));
+    a.kept_only = mac;
+    if (mac) return cci::sparse_mac_supports(a);
+    if (chosen == CCI_ALGO_DENSE_TILE_MFMA) return mac_next || cci::dense_tile_supports(a);
     return chosen == CCI_ALGO_NARROW_MFMA || chosen == CCI_ALGO_TAP_TILE_MFMA;
   };
   // Few 64 x 32 tiles: the split-reduction kernels (us, split / best other:

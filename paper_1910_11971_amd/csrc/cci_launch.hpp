@@ -57,6 +57,8 @@ struct ProductArgs {
   DType y_t;
   bool ragged = false;   // AUTO: also the forms that the tap-chunk and split-reduction families
                          // refuse when pinned
+  bool kept_only = false;  // a non-finite X reaches only the outputs that keep its column (a product
+                           // taken from the sparse-MAC kernels)
 };
 
 hipError_t launch_pack(const float* W, int64_t O, int64_t C, int32_t G, int32_t K,

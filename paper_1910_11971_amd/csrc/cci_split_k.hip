@@ -38,6 +38,7 @@
 #include <type_traits>
 
 #include "cci_device.hpp"
+#include "cci_kept.hpp"
 #include "cci_launch.hpp"
 
 namespace cci {
@@ -63,7 +64,7 @@ struct KParams {
   const float* bias;
   const void* residual;
   void* Y;
-  int32_t N, C, O, G, relu;
+  int32_t N, C, O, G, relu, kept_only;
   int32_t nob;    // output blocks (O / (16 OF), rounded up)
   int32_t tiles;  // row blocks x output blocks
   int32_t tpx;    // tiles per XCD (ceil(tiles / 8))
@@ -326,10 +327,11 @@ __global__ __launch_bounds__(kThreads) void split_k_kernel(KParams p) {
   // ---- epilogue: thread -> (row, 8 consecutive outputs)
   constexpr int kPerRow = TO / 8;
   const int32_t tid = static_cast<int32_t>(threadIdx.x);
+  static_assert(TR * kPerRow % 64 == 0, "whole waves have rows");
   if (tid >= TR * kPerRow) return;
   const int32_t nl = tid / kPerRow, ol = (tid % kPerRow) * 8;
   const int32_t n = n0 + nl, o = o0 + ol;
-  if (n >= p.N || o >= p.O) return;  // (O % 8 == 0: all 8 outputs or none)
+  const bool live = n < p.N && o < p.O;  // (O % 8 == 0: all 8 outputs or none)
   float y[8];
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
@@ -339,6 +341,8 @@ __global__ __launch_bounds__(kThreads) void split_k_kernel(KParams p) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) y[4 * h + e] = sum[e];
   }
+  if (p.kept_only) keep_kept<CONV>(y, p, K, n, o, live);
+  if (!live) return;
   if (p.scale) {
     const f32x4_t sc0 = *reinterpret_cast<const f32x4_t*>(&sb[0][ol]);
     const f32x4_t sc1 = *reinterpret_cast<const f32x4_t*>(&sb[0][ol + 4]);
@@ -530,6 +534,7 @@ hipError_t launch_split_k(const ProductArgs& a, hipStream_t s) {
   p.O = static_cast<int32_t>(a.O);
   p.G = a.G;
   p.relu = a.relu;
+  p.kept_only = a.kept_only;
   if (!plain_rows(a)) {
     const ConvGeom& g = a.geom;
     p.x_bytes = static_cast<uint32_t>(a.B * g.H * g.W * g.Cin * 2);

@@ -39,6 +39,7 @@
 
 #include "cci_chunks.hpp"
 #include "cci_device.hpp"
+#include "cci_kept.hpp"
 #include "cci_launch.hpp"
 
 namespace cci {
@@ -84,7 +85,7 @@ struct TParams {
   const void* residual;
   void* Y;
   uint32_t x_bytes, v_bytes, i_bytes, y_bytes;
-  int32_t N, C, O, G, K, relu;
+  int32_t N, C, O, G, K, relu, kept_only;
   int32_t npb, nob, nch;  // pixel blocks (of 128), output blocks (of TO), chunks
   int32_t cpt;            // chunks per tap: Cin / 64
   int32_t full, rag_k8;   // whole chunks (C / 64), and the 8-column blocks after them
@@ -611,6 +612,19 @@ __device__ __forceinline__ void tap_tile_body(const TParams& p, uint8_t* const l
     });
   }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this wave's staging writes have landed
+  if (p.kept_only) {  // (a lane reads back what it owns: no other lane waits for it)
+#pragma unroll 1
+    for (int rr = 0; rr < NPS; ++rr) {
+      f32x4_t* const src = reinterpret_cast<f32x4_t*>(stg + (RPP * rr + lane / LPR) * PITCH + c8 * 32);
+      const f32x4_t h0 = src[0], h1 = src[1];
+      float y[8] = {h0[0], h0[1], h0[2], h0[3], h1[0], h1[1], h1[2], h1[3]};
+      const uint32_t px = pb * kTP + static_cast<uint32_t>(wp * 64 + 16 * NPT * team + RPP * rr + lane / LPR);
+      keep_kept<true>(y, p, p.K, static_cast<int32_t>(px), static_cast<int32_t>(o),
+                      px < static_cast<uint32_t>(p.N) && o_ok);
+      src[0] = f32x4_t{y[0], y[1], y[2], y[3]};
+      src[1] = f32x4_t{y[4], y[5], y[6], y[7]};
+    }
+  }
 #pragma unroll
   for (int rr = 0; rr < NPS; ++rr) {
     const int row = RPP * rr + lane / LPR;
@@ -790,6 +804,7 @@ hipError_t launch_tap_tile(const ProductArgs& a, hipStream_t s) {
   p.G = a.G;
   p.K = a.K;
   p.relu = a.relu;
+  p.kept_only = a.kept_only;
   p.npb = static_cast<int32_t>((a.N + kTP - 1) / kTP);
   // 128-output tiles, unless they would leave more than half of the CUs idle
   // or one of them would be more than half empty (us, 128 / 64 outputs:

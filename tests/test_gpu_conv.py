@@ -243,6 +243,32 @@ def test_conv_ragged_auto(B, H, W, Cin, O, k, stride, pad, G, K):
              torch.bfloat16, "auto", ep=ep)
 
 
+@pytest.mark.parametrize("B,H,W,Cin,O,k,stride,pad,G,K", [
+    (2, 9, 11, 96, 64, 3, 2, 1, 32, 1), (1, 17, 13, 328, 72, 1, 2, 0, 8, 3),  # split-reduction: taps, a strided 1x1
+    (20, 40, 41, 328, 136, 1, 2, 0, 8, 2),  # tap-chunk
+])
+def test_conv_auto_nonfinite_reaches_kept_columns_only(B, H, W, Cin, O, k, stride, pad, G, K):
+    """As in the products of plain rows: an infinity or NaN of a pixel reaches the outputs that keep its column under
+    some tap, and the padding is finite."""
+    need_gpu()
+    from paper_1910_11971_amd import cci
+    vals, idx = cci.pack(torch.from_numpy(rand_w(O, k * k * Cin, 133 + G)).to(DEV), G, K, torch.bfloat16)
+    X = rand_x((B, H, W, Cin), torch.bfloat16, 5 * Cin).to(DEV)
+    X[0, 0, 0, 3] = float("inf")
+    X[B - 1, H - 1, W - 1, Cin - 1] = float("nan")
+    X[0, 4, 6, 5] = float("-inf")
+    X[B - 1, H // 2 // 2 * 2, 2] = float("nan")
+    args = (X, vals, idx, G, k, k, (stride, stride), (pad, pad))
+    Y = cci.conv_im2col(*args, out_dtype=torch.float32)
+    want = cci.conv_im2col(*args, out_dtype=torch.float32, algo="sparse_mac")
+    assert not torch.isfinite(want).all() and torch.isfinite(want[0, 0, 0]).any()
+    assert int((torch.isnan(Y) != torch.isnan(want)).sum()) == 0
+    assert int(((Y != want) & (torch.isinf(Y) | torch.isinf(want))).sum()) == 0
+    ok = torch.isfinite(want)
+    mag = cci.conv_im2col(X.nan_to_num(0, 0, 0).abs(), vals.abs(), *args[2:], out_dtype=torch.float32, algo="sparse_mac")
+    assert ((Y - want).abs()[ok] <= (k * k * Cin * 2.0 ** -23 * mag)[ok]).all()  # fp32 sums of exact products
+
+
 @pytest.mark.parametrize("KH,KW,Cin,G", [(3, 3, 705184, 8), (5, 5, 424032, 32), (4, 8, 372064, 32)])
 def test_conv_split_k_very_long_taps(KH, KW, Cin, G):
     """The tap of the last k-step of the last tap: Cin from which a rounded-up reciprocal of Cin / 32 gives the next one."""

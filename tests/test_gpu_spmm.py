@@ -387,3 +387,42 @@ def test_spmm_fp32_few_rows(N, C, O, G, K):
     need_gpu()
     ep = rand_epilogue(O, N, torch.float32, N + C, residual=True, relu=True)
     run_case(rand_x(N, C, torch.float32, N), rand_w(O, C, C), G, K, torch.float32, "auto", ep=ep)
+
+
+# bf16 products whose reduction the MFMA families did not take whole once (C % 32 != 0 over 256 columns, or few kept
+# rows in wide groups): split-reduction (whole and short last k-step, weights in LDS and not), tap-chunk (one team, two)
+SPARSE_TERM_CASES = [(130, 296, 48, 8, 2), (100, 1000, 144, 16, 4), (70, 3272, 16, 2, 1), (196, 320, 64, 32, 1),
+                     (9000, 360, 136, 8, 3), (40000, 264, 136, 4, 2), (6000, 1336, 64, 16, 8)]
+
+
+@pytest.mark.parametrize("y_dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("N,C,O,G,K", SPARSE_TERM_CASES)
+def test_spmm_auto_nonfinite_reaches_kept_columns_only(N, C, O, G, K, y_dtype):
+    """An infinity or NaN of X reaches the outputs that keep its column, as on the sparse-MAC kernels, not every output
+    of its row."""
+    need_gpu()
+    from paper_1910_11971_amd import cci
+    vals, idx = cci.pack(torch.from_numpy(rand_w(O, C, O + G)).to(DEV), G, K, torch.bfloat16)
+    X = rand_x(N, C, torch.bfloat16, N + C).to(DEV)
+    rows = torch.arange(0, N, 7, device=DEV)
+    g = torch.Generator().manual_seed(C)
+    cols = torch.randint(0, C, (len(rows),), generator=g).to(DEV)
+    bad = torch.tensor([float("inf"), float("-inf"), float("nan")], device=DEV).bfloat16()
+    X[rows, cols] = bad[torch.arange(len(rows), device=DEV) % 3]
+    X[1] = float("nan")  # a whole row
+    X[N - 1, C - 1] = float("inf")
+    X[N - 1, 0] = float("-inf")
+    s, b, r, r_t, _ = rand_epilogue(O, N, y_dtype, N + O, residual=True)
+    kw = dict(scale=torch.from_numpy(s).to(DEV), bias=torch.from_numpy(b).to(DEV), residual=r_t.to(DEV), out_dtype=y_dtype)
+    for relu in (False, True):
+        Y = cci.spmm(X, vals, idx, G, relu=relu, **kw).float()
+        want = cci.spmm(X, vals, idx, G, relu=relu, algo="sparse_mac", **kw).float()
+        assert torch.isfinite(want).any(1)[0]
+        assert int((torch.isnan(Y) != torch.isnan(want)).sum()) == 0
+        assert int(((Y != want) & (torch.isinf(Y) | torch.isinf(want))).sum()) == 0
+        ok = torch.isfinite(want)
+        # both sum the same exact products in fp32 (any order) and round once to Y's type
+        tol = C * 2.0 ** -23 + (2.0 ** -7 if y_dtype == torch.bfloat16 else 0.0)
+        mag = cci.spmm(X.nan_to_num(0, 0, 0).abs(), vals.abs(), idx, G, out_dtype=torch.float32, algo="sparse_mac") * \
+            kw["scale"] + kw["bias"].abs() + kw["residual"].float().abs()
+        assert ((Y - want).abs()[ok] <= (tol * mag)[ok]).all()
