@@ -165,14 +165,13 @@ def main():
     idx = torch.empty((wl.O // wl.G, wl.K, wl.C), dtype=torch.uint8, device=dev)
 
     stream = torch.cuda.Stream(device=dev)  # default priority
-    algo = args.algo if args.algo != "auto" else cci.auto_algo(xdt, vdt, wl.N, wl.C, wl.Cin, wl.O, wl.G, wl.K)
 
     def conv_only(i):  # the product (a convolution, or an FC layer via cci_spmm)
         if wl.conv:
-            cci.conv_im2col(Xs[i % ncopy], vals, idx, wl.G, wl.KH, wl.KW, stride, pad, out_dtype=ydt, algo=algo,
+            cci.conv_im2col(Xs[i % ncopy], vals, idx, wl.G, wl.KH, wl.KW, stride, pad, out_dtype=ydt, algo=args.algo,
                             out=Ys[i % ncopy])
         else:
-            cci.spmm(Xs[i % ncopy], vals, idx, wl.G, out_dtype=ydt, algo=algo, out=Ys[i % ncopy])
+            cci.spmm(Xs[i % ncopy], vals, idx, wl.G, out_dtype=ydt, algo=args.algo, out=Ys[i % ncopy])
 
     def step(i):
         cci.pack(W, wl.G, wl.K, vdt, out=(vals, idx))
@@ -226,6 +225,7 @@ def main():
     # each kernel alone, the same number of launches back to back (graph replays)
     conv_avg = _graph_time(conv_only, ncopy_g, max(1, args.steps // ncopy_g), stream)
     pack_avg = _graph_time(pack_only, 16, max(1, args.steps // 16), stream)
+    algo = cci.last_algo()  # the family that the timed products ran on
 
     flop = 2.0 * wl.N * wl.nnz
     value = flop / (ms_step * 1e-3) / 1e12
@@ -622,11 +622,11 @@ def main_fc_sweep(args):
         idx = torch.empty((wl.O // wl.G, K, wl.C), dtype=torch.uint8, device=dev)
         with torch.cuda.stream(stream):
             cci.pack(W, wl.G, K, torch.bfloat16, out=(vals, idx))
-        algo = cci.auto_algo(torch.bfloat16, torch.bfloat16, wl.N, wl.C, wl.Cin, wl.O, wl.G, K)
         prod = (lambda i, vals=vals, idx=idx, G=wl.G: cci.spmm(Xs[i % ncopy], vals, idx, G,
                                                                out_dtype=torch.bfloat16, out=Ys[i % ncopy]))
         pack = (lambda i, vals=vals, idx=idx, G=wl.G, K=K: cci.pack(W, G, K, torch.bfloat16, out=(vals, idx)))
         t_prod = _graph_time(prod, ncopy, max(2, 90 // ncopy), stream)
+        algo = cci.last_algo()
         t_pack = _graph_time(pack, 8, 8, stream)
         flop = 2.0 * wl.N * wl.nnz
         dense_flop = 2.0 * wl.N * wl.C * wl.O
@@ -849,8 +849,6 @@ def sweep(args):
             Ys = [torch.empty((wl.N, wl.O), dtype=ydt, device=dev) for _ in range(ncopy)]
         W = torch.from_numpy(W_np).to(dev)
         vals, idx = cci.pack(W, wl.G, wl.K, xdt)
-        algo = cci.auto_algo(xdt, xdt, wl.N, wl.C, wl.Cin, wl.O, wl.G, wl.K)
-        kname = kernel_name(algo)
         if wl.conv:
             f = lambda i: cci.conv_im2col(Xs[i % ncopy], vals, idx, wl.G, wl.KH, wl.KW, (wl.stride,) * 2,
                                           (wl.pad,) * 2, out_dtype=ydt, out=Ys[i % ncopy])
@@ -858,6 +856,8 @@ def sweep(args):
             f = lambda i: cci.spmm(Xs[i % ncopy], vals, idx, wl.G, out_dtype=ydt, out=Ys[i % ncopy])
         n_launch = max(ncopy, 8)
         t_cci = _graph_time(f, n_launch, max(2, 200 // n_launch), stream)
+        algo = cci.last_algo()
+        kname = kernel_name(algo)
         t_pack = _graph_time(lambda i: cci.pack(W, wl.G, wl.K, xdt, out=(vals, idx)), 16, 10, stream)
         flop = 2.0 * wl.N * wl.nnz
         dense_flop = 2.0 * wl.N * wl.C * wl.O
@@ -991,7 +991,7 @@ def sweep_mobilenetv2(stream, K, B=64):
         flop += 2.0 * w.N * w.nnz
         dense_flop += 2.0 * w.N * w.C * w.O
         alg_bytes += 2.0 * w.N * (w.C + w.O) + 3.0 * w.nnz
-    algos = [cci.auto_algo(torch.bfloat16, torch.bfloat16, w.N, w.C, w.Cin, w.O, w.G, w.K) for w in P]
+    algos = []  # the family each layer runs on
 
     def layer(i, algo="auto"):
         w = P[i]
@@ -1012,6 +1012,7 @@ def sweep_mobilenetv2(stream, K, B=64):
     per_layer = []
     for i, w in enumerate(P):
         t = _graph_time(lambda _j, i=i: layer(i), 8, 5, stream)
+        algos.append(cci.last_algo())
         row = [w.name[5:], w.N, w.C, w.O, algos[i], round(t * 1e3, 2)]
         alt = {}
         for a in ("narrow_mfma", "dense_tile_mfma"):  # the other MFMA kernels that take the shape

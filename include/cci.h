@@ -234,27 +234,24 @@ cci_status cci_conv_im2col_algo(const void *X, cci_dtype x_t, int64_t B,
                                 void *Y, cci_dtype y_t, cci_algo algo,
                                 void *stream);
 
-/* Which family CCI_ALGO_AUTO picks for a product of N x C x O (conv: pass
- * N = B*Ho*Wo, C = KH*KW*Cin and cin = Cin; FC: cin = C).  Host-only.  A
- * 1x1 convolution reported as CCI_ALGO_WIDE_TILE_MFMA runs on the tap-chunk
- * kernels (else the dense-tile ones) when its stride or padding rules the
- * wide-tile ones out; one reported as CCI_ALGO_NARROW_MFMA then runs on the
- * dense-tile kernels if they take its shape, else on the sparse-MAC ones;
- * one reported as CCI_ALGO_RESIDENT_MFMA or CCI_ALGO_TAP_TILE_MFMA runs on
- * the dense-tile kernels when a stride, alignment or size limit of that
- * family rules it out; one reported as CCI_ALGO_STREAM_TILE_MFMA runs on the
- * tap-chunk kernels (else the dense-tile ones) when its stride, padding or
- * alignment rules the streaming ones out; one reported as
- * CCI_ALGO_SPLIT_K_MFMA runs on the dense-tile kernels when its stride,
- * padding or alignment rules the split-reduction ones out.  And one
- * reported as CCI_ALGO_NARROW_MFMA, CCI_ALGO_DENSE_TILE_MFMA,
- * CCI_ALGO_TAP_TILE_MFMA or CCI_ALGO_SPARSE_MAC runs on the split-reduction
- * kernels when it has few output tiles, or on the tap-chunk ones when its
- * reduction has 96 or more columns, also in ragged forms that cannot be
- * pinned: reductions in blocks of 8 (one tap), O % 8 == 0, and (split-
- * reduction) convolutions of any geometry. */
+/* Which family the shape rules of CCI_ALGO_AUTO name for a product of N x C
+ * x O (conv: pass N = B*Ho*Wo, C = KH*KW*Cin and cin = Cin; FC: cin = C).
+ * Host-only.  A call also sees stride, padding, alignment and size, and may
+ * run on another family: where those rule the named one out, on the tap-chunk
+ * kernels (from the wide-tile and streaming ones) or the dense-tile, then the
+ * sparse-MAC ones; and a product that this leaves to the narrow, dense-tile,
+ * tap-chunk or sparse-MAC kernels runs on the split-reduction kernels when it
+ * has few output tiles, or on the tap-chunk ones when its reduction has 96
+ * or more columns, also in ragged forms that cannot be pinned: reductions in
+ * blocks of 8 (one tap), O % 8 == 0, and (split-reduction) convolutions of
+ * any geometry.  cci_last_algo tells what ran. */
 cci_algo cci_auto_algo(cci_dtype x_t, cci_dtype val_t, int64_t N, int64_t C,
                        int64_t cin, int64_t O, int32_t G, int32_t K);
+
+/* The family that the calling thread's last cci_spmm / cci_conv_im2col call
+ * (plain or _algo) with rows to compute launched or tried to launch:
+ * CCI_ALGO_AUTO before the first.  A refused call leaves it as it was. */
+cci_algo cci_last_algo(void);
 
 /* ------------------------------------------------------------------------
  * Balanced sparsity (Sec. 2.4, Sec. 3.3, Fig. 2b): the paper's comparison

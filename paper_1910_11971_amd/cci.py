@@ -74,6 +74,8 @@ _lib.cci_spmm_bits.argtypes = [_vp, ctypes.c_int, _i64, _i64, _vp, ctypes.c_int,
                                ctypes.POINTER(Epilogue), _vp, ctypes.c_int, _vp]
 _lib.cci_auto_algo.argtypes = [ctypes.c_int, ctypes.c_int, _i64, _i64, _i64, _i64, _i32, _i32]
 _lib.cci_auto_algo.restype = ctypes.c_int
+_lib.cci_last_algo.argtypes = []
+_lib.cci_last_algo.restype = ctypes.c_int
 _lib.cci_maxpool2d_nhwc.argtypes = [_vp, ctypes.c_int, _i64, _i64, _i64, _i64, _i32, _i32, _i32, _vp, _vp]
 _lib.cci_global_avgpool_nhwc.argtypes = [_vp, ctypes.c_int, _i64, _i64, _i64, _i64, _vp, ctypes.c_int, _vp]
 _lib.cci_status_str.argtypes = [ctypes.c_int]
@@ -254,9 +256,17 @@ def conv_im2col(X: torch.Tensor, vals: torch.Tensor, idx: torch.Tensor, G: int, 
     return Y
 
 
+def _algo_name(code: int) -> str:
+    return next(name for name, v in ALGOS.items() if v == code)
+
+
 def auto_algo(x_dtype, val_dtype, N, C, cin, O, G, K) -> str:
-    code = _lib.cci_auto_algo(_code(x_dtype), _code(val_dtype), N, C, cin, O, G, K)
-    return {v: k for k, v in ALGOS.items()}[code]
+    return _algo_name(_lib.cci_auto_algo(_code(x_dtype), _code(val_dtype), N, C, cin, O, G, K))
+
+
+def last_algo() -> str:
+    """cci_last_algo: the kernel family of this thread's last spmm / conv_im2col call."""
+    return _algo_name(_lib.cci_last_algo())
 
 
 def maxpool2d_nhwc(X: torch.Tensor, k: int, s: int, p: int) -> torch.Tensor:

@@ -1,6 +1,6 @@
 // C ABI of the CCI library: argument validation, kernel-family choice and
 // error reporting.  Nothing here allocates, synchronises or keeps state other
-// than the calling thread's last error message.
+// than the calling thread's last error message and kernel family.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -14,6 +14,7 @@
 namespace {
 
 thread_local char g_last_error[512] = "";
+thread_local cci_algo g_last_algo = CCI_ALGO_AUTO;
 
 cci_status fail(cci_status s, const char* fmt, ...) {
   va_list ap;
@@ -204,6 +205,7 @@ cci_status run_product(cci::ProductArgs& a, cci_algo algo, const cci_epilogue* e
     return fail(CCI_EUNSUPPORTED,
                 "split-K MFMA kernels need bf16 X/vals, an FC or stride-1 unpadded 1x1 product, "
                 "C %% 32 == 0, O %% 16 == 0, K <= 4 and 16-byte aligned pointers");
+  g_last_algo = chosen;
   const hipStream_t st = static_cast<hipStream_t>(stream);
   hipError_t e = chosen == CCI_ALGO_SPARSE_MAC       ? cci::launch_sparse_mac(a, st)
                  : chosen == CCI_ALGO_SPLIT_K_MFMA   ? cci::launch_split_k(a, st)
@@ -402,6 +404,8 @@ cci_algo cci_auto_algo(cci_dtype x_t, cci_dtype val_t, int64_t N, int64_t C, int
   if (tile_shape && (32 * static_cast<int64_t>(K) > G || !mac_g)) return CCI_ALGO_DENSE_TILE_MFMA;
   return CCI_ALGO_SPARSE_MAC;
 }
+
+cci_algo cci_last_algo(void) { return g_last_algo; }
 
 cci_status cci_spmm_algo(const void* X, cci_dtype x_t, int64_t N, int64_t C, const void* vals,
                          cci_dtype val_t, const uint8_t* idx, int64_t O, int32_t G, int32_t K,

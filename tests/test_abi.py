@@ -343,3 +343,24 @@ def test_index_width_host_logic_and_bits_validation():
                              None) == cci.EUNSUPPORTED
     assert lib.cci_spmm_bits(None, cci.BF16, 0, 64, None, cci.BF16, None, 4, 64, 16, 2, None, None, cci.BF16,
                              None) == cci.OK
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="the pointers are not memory: a call must end at the launch")
+def test_last_algo_names_the_family_of_a_call():
+    """The family a call ran on is not the shape rules' one alone; a refused call leaves it."""
+    fc = lambda N, C, O, G, K, t=cci.BF16: lib.cci_spmm(FAKE, t, N, C, FAKE, t, FAKE, O, G, K, None, FAKE, t, None)
+    for args, rule, family in [((49, 1352, 232, 8, 2), "sparse_mac", "split_k_mfma"),
+                               ((9000, 824, 136, 8, 4), "sparse_mac", "tap_tile_mfma"),
+                               ((5000, 120, 72, 8, 1), "narrow_mfma", "split_k_mfma"),
+                               ((6000, 120, 72, 8, 1), "narrow_mfma", "tap_tile_mfma"),
+                               ((64, 4096, 4096, 16, 4), "few_rows_mfma", "few_rows_mfma")]:
+        N, C, O, G, K = args
+        assert cci.auto_algo(torch.bfloat16, torch.bfloat16, N, C, C, O, G, K) == rule
+        assert fc(*args) == cci.EHIP  # no device here
+        assert cci.last_algo() == family
+    assert fc(64, 256, 256, 8, 4, cci.F32) == cci.EHIP and cci.last_algo() == "sparse_mac"
+    assert fc(100, 300, 96, 6, 2) == cci.EUNSUPPORTED and cci.last_algo() == "sparse_mac"
+    # a strided 3x3 convolution over 64 channels: the resident kernels take unit strides only
+    assert lib.cci_conv_im2col(FAKE, cci.BF16, 9, 30, 30, 64, 3, 3, 2, 2, 1, 1, FAKE, cci.BF16, FAKE, 64, 8, 2, None,
+                               FAKE, cci.BF16, None) == cci.EHIP
+    assert cci.last_algo() == "split_k_mfma"

@@ -226,28 +226,36 @@ def test_conv_tap_tile_epilogue(y_dtype):
              "tap_tile_mfma", ep=ep)
 
 
-@pytest.mark.parametrize("B,H,W,Cin,O,k,stride,pad,G,K", [
-    (9, 30, 30, 64, 64, 3, 2, 1, 8, 2), (20, 28, 28, 64, 96, 3, 1, 1, 8, 2),  # 64- and 96-output tiles, taps
-    (40, 17, 19, 136, 72, 1, 2, 0, 8, 4), (8, 30, 31, 72, 200, 1, 1, 1, 8, 2),  # strided / padded 1x1, short chunk
-    (9, 14, 14, 256, 256, 3, 1, 1, 8, 2), (60, 9, 9, 64, 136, 3, 1, 1, 8, 4),  # two teams starting inside a filter row
-    # split-reduction: taps of 1, 3 and 8 k-steps, strides, no and wide padding, ragged outputs, a strided short reduction
+# Convolutions AUTO gives to the tap-chunk and split-reduction kernels' ragged forms
+RAGGED_CASES = [("tap_tile_mfma", c) for c in [  # B, H, W, Cin, O, k, stride, pad, G, K
+    (40, 30, 30, 64, 64, 3, 2, 1, 8, 2), (20, 28, 28, 64, 96, 3, 1, 1, 8, 2),  # 64- and 96-output tiles, taps
+    (70, 17, 19, 136, 72, 1, 2, 0, 8, 4), (8, 30, 31, 104, 200, 1, 1, 1, 8, 2),  # strided / padded 1x1, short chunk
+    (12, 14, 14, 256, 256, 3, 1, 1, 8, 2), (60, 9, 9, 64, 136, 3, 1, 1, 8, 4),  # two teams starting inside a filter row
+]] + [("split_k_mfma", c) for c in [
+    # taps of 1, 3 and 8 k-steps, strides, no and wide padding, ragged outputs, a strided short reduction
     (1, 14, 14, 256, 256, 3, 1, 1, 8, 2), (2, 15, 13, 32, 48, 5, 2, 2, 4, 1), (1, 9, 20, 96, 40, 3, 2, 0, 8, 3),
     (3, 11, 7, 72, 136, 1, 2, 0, 8, 4), (1, 7, 7, 512, 512, 3, 1, 1, 8, 4), (1, 6, 5, 64, 64, 3, 2, 2, 16, 2),
-])
-def test_conv_ragged_auto(B, H, W, Cin, O, k, stride, pad, G, K):
-    """Convolutions AUTO gives to the tap-chunk and split-reduction kernels' ragged forms."""
+    (9, 30, 30, 64, 64, 3, 2, 1, 8, 2), (40, 17, 19, 136, 72, 1, 2, 0, 8, 4), (9, 14, 14, 256, 256, 3, 1, 1, 8, 2),
+]] + [("narrow_mfma", (8, 30, 31, 72, 200, 1, 1, 1, 8, 2))]
+
+
+@pytest.mark.parametrize("family,case", RAGGED_CASES)
+def test_conv_ragged_auto(family, case):
     need_gpu()
+    from paper_1910_11971_amd import cci
+    B, H, W, Cin, O, k, stride, pad, G, K = case
     Ho, Wo = (H + 2 * pad - k) // stride + 1, (W + 2 * pad - k) // stride + 1
     ep = rand_epilogue(O, B * Ho * Wo, torch.bfloat16, 131 + Cin, residual=True, relu=True)
     run_conv(rand_x((B, H, W, Cin), torch.bfloat16, 132 + O), rand_w(O, k * k * Cin, 133 + G), G, K, k, stride, pad,
              torch.bfloat16, "auto", ep=ep)
+    assert cci.last_algo() == family
 
 
-@pytest.mark.parametrize("B,H,W,Cin,O,k,stride,pad,G,K", [
-    (2, 9, 11, 96, 64, 3, 2, 1, 32, 1), (1, 17, 13, 328, 72, 1, 2, 0, 8, 3),  # split-reduction: taps, a strided 1x1
-    (20, 40, 41, 328, 136, 1, 2, 0, 8, 2),  # tap-chunk
+@pytest.mark.parametrize("family,B,H,W,Cin,O,k,stride,pad,G,K", [
+    ("split_k_mfma", 2, 9, 11, 96, 64, 3, 2, 1, 32, 1), ("split_k_mfma", 1, 17, 13, 328, 72, 1, 2, 0, 8, 3),
+    ("tap_tile_mfma", 20, 40, 41, 328, 136, 1, 2, 0, 8, 2),
 ])
-def test_conv_auto_nonfinite_reaches_kept_columns_only(B, H, W, Cin, O, k, stride, pad, G, K):
+def test_conv_auto_nonfinite_reaches_kept_columns_only(family, B, H, W, Cin, O, k, stride, pad, G, K):
     """As in the products of plain rows: an infinity or NaN of a pixel reaches the outputs that keep its column under
     some tap, and the padding is finite."""
     need_gpu()
@@ -260,6 +268,7 @@ def test_conv_auto_nonfinite_reaches_kept_columns_only(B, H, W, Cin, O, k, strid
     X[B - 1, H // 2 // 2 * 2, 2] = float("nan")
     args = (X, vals, idx, G, k, k, (stride, stride), (pad, pad))
     Y = cci.conv_im2col(*args, out_dtype=torch.float32)
+    assert cci.last_algo() == family
     want = cci.conv_im2col(*args, out_dtype=torch.float32, algo="sparse_mac")
     assert not torch.isfinite(want).all() and torch.isfinite(want[0, 0, 0]).any()
     assert int((torch.isnan(Y) != torch.isnan(want)).sum()) == 0
@@ -285,6 +294,7 @@ def test_conv_split_k_very_long_taps(KH, KW, Cin, G):
     X = torch.zeros(1, H, W, Cin, device=DEV, dtype=torch.bfloat16)
     X[..., -64:] = torch.randn(1, H, W, 64, device=DEV, generator=g).bfloat16()
     Y = cci.conv_im2col(X, vals, idx, G, KH, KW, (1, 1), pad, out_dtype=torch.float32)
+    assert cci.last_algo() == "split_k_mfma"
     v = torch.zeros(O, KH * KW * Cin, device=DEV).scatter_(0, idx.long().view(1, -1), vals.float().view(1, -1))
     v = v.view(O, KH, KW, Cin)[..., -64:].permute(0, 3, 1, 2).double().cpu()
     x = X[..., -64:].permute(0, 3, 1, 2).double().cpu()

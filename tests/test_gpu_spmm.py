@@ -115,37 +115,46 @@ def test_spmm_bf16_tap_tile(N, C, O, G, K):
     run_case(rand_x(N, C, torch.bfloat16, N + C), rand_w(O, C, O + G), G, K, torch.bfloat16, "tap_tile_mfma")
 
 
-RAGGED_CASES = [  # N, C, O, G, K: products AUTO gives to the tap-chunk and split-reduction kernels' ragged forms
-    # tap-chunk: 1, 7 and 0 column blocks in the last chunk, 8 outputs in the last tile, both tile widths
-    (6000, 136, 816, 8, 2), (9000, 824, 136, 8, 4), (5000, 120, 72, 8, 1), (20000, 104, 264, 8, 3),
-    (3000, 1336, 520, 4, 2), (2500, 96, 1000, 8, 8), (2000, 2040, 1000, 8, 2), (9001, 200, 24, 2, 1),
+# Products AUTO gives to the tap-chunk and split-reduction kernels' ragged forms
+RAGGED_CASES = [("tap_tile_mfma", c) for c in [  # N, C, O, G, K
+    # 1, 7 and 0 column blocks in the last chunk, 8 outputs in the last tile, both tile widths
+    (6000, 136, 816, 8, 2), (9000, 824, 136, 8, 4), (6000, 120, 72, 8, 1), (20000, 104, 264, 8, 3),
+    (3000, 1336, 520, 4, 2), (2500, 96, 1000, 8, 8), (2000, 2040, 1000, 8, 2), (17000, 200, 24, 2, 1),
     (6000, 136, 256, 32, 7),
     # two teams: an odd number of chunks (the second team's last one is empty), a short chunk before it
     (300, 320, 1008, 16, 8), (300, 1480, 1008, 16, 16), (257, 264, 1032, 8, 8), (40, 1040, 2056, 8, 8),
-    # split-reduction: 8, 16 and 24 columns in the last k-step, rows of 8-byte index units, 8 outputs in the last tile
+]] + [("split_k_mfma", c) for c in [
+    # 8, 16 and 24 columns in the last k-step, rows of 8-byte index units, 8 outputs in the last tile
     (49, 1352, 232, 8, 2), (130, 72, 40, 8, 1), (65, 88, 24, 4, 2), (300, 1000, 136, 8, 4), (33, 2072, 56, 8, 3),
-    (100, 5000, 48, 16, 4), (70, 1016, 320, 32, 2),
-]
+    (100, 5000, 48, 16, 4), (70, 1016, 320, 32, 2), (5000, 120, 72, 8, 1), (9001, 200, 24, 2, 1),
+]]
 
 
-@pytest.mark.parametrize("N,C,O,G,K", RAGGED_CASES)
-def test_spmm_bf16_ragged_auto(N, C, O, G, K):
+@pytest.mark.parametrize("family,case", RAGGED_CASES)
+def test_spmm_bf16_ragged_auto(family, case):
     need_gpu()
+    from paper_1910_11971_amd import cci
+    N, C, O, G, K = case
     ep = rand_epilogue(O, N, torch.bfloat16, N + O, residual=N % 2 == 0, relu=True)
     run_case(rand_x(N, C, torch.bfloat16, N + C), rand_w(O, C, O + G), G, K, torch.bfloat16, "auto", ep=ep)
+    assert cci.last_algo() == family
     run_case(rand_x(N, C, torch.bfloat16, N + C), rand_w(O, C, O + G), G, K, torch.float32, "auto")
+    assert cci.last_algo() == family
 
 
 @pytest.mark.parametrize("N,C,O,G", [(20000, 264, 8, 8), (17000, 776, 16, 16), (20000, 272, 8, 4)])
 def test_spmm_ragged_single_packed_row(N, C, O, G):
     """One or two packed rows and a second team whose last chunk is empty: its uniform offset would be past them."""
     need_gpu()
+    from paper_1910_11971_amd import cci
     rows = np.unique(np.concatenate([np.arange(0, 256), np.arange(N - 200, N), np.arange(0, N, 97)]))
     run_case(rand_x(N, C, torch.bfloat16, N + C), rand_w(O, C, O + G), G, 1, torch.float32, "auto", rows=rows)
+    assert cci.last_algo() == "tap_tile_mfma"
 
 
-@pytest.mark.parametrize("N,C,O", [(3000, 136, 136), (130, 72, 48)])  # tap-chunk, split-reduction
-def test_spmm_ragged_reduction_keeps_neighbours_out(N, C, O):
+@pytest.mark.parametrize("N,C,O,family", [(6000, 136, 136, "tap_tile_mfma"), (6000, 248, 136, "tap_tile_mfma"),
+                                          (3000, 136, 136, "split_k_mfma"), (130, 72, 48, "split_k_mfma")])
+def test_spmm_ragged_reduction_keeps_neighbours_out(N, C, O, family):
     """The columns past a ragged reduction are another packed row's (here all infinite) and X's next row: neither may
     reach this row's sums."""
     need_gpu()
@@ -158,6 +167,7 @@ def test_spmm_ragged_reduction_keeps_neighbours_out(N, C, O):
     X = rand_x(N, C, torch.bfloat16, 6).to(DEV)
     X[1::2] = float("nan")
     Y = cci.spmm(X, vals, idx, G)
+    assert cci.last_algo() == family
     even = Y.view(N, O // G, G)[0::2, 0::2].float()
     want = ref.view(N, O // G, G)[0::2, 0::2].float()
     assert torch.isfinite(even).all()
@@ -365,13 +375,11 @@ def test_spmm_sparse_mac_small_n_wide_groups(N, C, O, G, K, xdt):
     run_case(rand_x(N, C, xdt, N + 3), rand_w(O, C, O + 5), G, K, xdt, "sparse_mac", ep=ep)
 
 
-@pytest.mark.parametrize("N,C,O,G,K", [(100, 1016, 320, 64, 2), (100, 136, 96, 6, 2)])
+@pytest.mark.parametrize("N,C,O,G,K", [(100, 1016, 320, 64, 2), (100, 300, 96, 6, 2)])
 def test_spmm_auto_still_refuses(N, C, O, G, K):
     """A product that no family took whole is not taken in a ragged form either."""
     need_gpu()
     from paper_1910_11971_amd import cci
-    if G == 6:
-        C, O = 300, 96  # past the narrow kernels' reduction
     vals, idx = cci.pack(torch.from_numpy(rand_w(O, C, 2)).to(DEV), G, K, torch.bfloat16)
     with pytest.raises(cci.CCIError):
         cci.spmm(rand_x(N, C, torch.bfloat16, 1).to(DEV), vals, idx, G)
@@ -391,17 +399,19 @@ def test_spmm_fp32_few_rows(N, C, O, G, K):
 
 # bf16 products whose reduction the MFMA families did not take whole once (C % 32 != 0 over 256 columns, or few kept
 # rows in wide groups): split-reduction (whole and short last k-step, weights in LDS and not), tap-chunk (one team, two)
-SPARSE_TERM_CASES = [(130, 296, 48, 8, 2), (100, 1000, 144, 16, 4), (70, 3272, 16, 2, 1), (196, 320, 64, 32, 1),
-                     (9000, 360, 136, 8, 3), (40000, 264, 136, 4, 2), (6000, 1336, 64, 16, 8)]
+SPARSE_TERM_CASES = [("split_k_mfma", c) for c in [(130, 296, 48, 8, 2), (100, 1000, 144, 16, 4), (70, 3272, 16, 2, 1),
+                                                   (196, 320, 64, 32, 1)]] + \
+                    [("tap_tile_mfma", c) for c in [(9000, 360, 136, 8, 3), (40000, 264, 136, 4, 2), (6000, 1336, 64, 16, 8)]]
 
 
 @pytest.mark.parametrize("y_dtype", [torch.bfloat16, torch.float32])
-@pytest.mark.parametrize("N,C,O,G,K", SPARSE_TERM_CASES)
-def test_spmm_auto_nonfinite_reaches_kept_columns_only(N, C, O, G, K, y_dtype):
+@pytest.mark.parametrize("family,case", SPARSE_TERM_CASES)
+def test_spmm_auto_nonfinite_reaches_kept_columns_only(family, case, y_dtype):
     """An infinity or NaN of X reaches the outputs that keep its column, as on the sparse-MAC kernels, not every output
     of its row."""
     need_gpu()
     from paper_1910_11971_amd import cci
+    N, C, O, G, K = case
     vals, idx = cci.pack(torch.from_numpy(rand_w(O, C, O + G)).to(DEV), G, K, torch.bfloat16)
     X = rand_x(N, C, torch.bfloat16, N + C).to(DEV)
     rows = torch.arange(0, N, 7, device=DEV)
@@ -416,6 +426,7 @@ def test_spmm_auto_nonfinite_reaches_kept_columns_only(N, C, O, G, K, y_dtype):
     kw = dict(scale=torch.from_numpy(s).to(DEV), bias=torch.from_numpy(b).to(DEV), residual=r_t.to(DEV), out_dtype=y_dtype)
     for relu in (False, True):
         Y = cci.spmm(X, vals, idx, G, relu=relu, **kw).float()
+        assert cci.last_algo() == family
         want = cci.spmm(X, vals, idx, G, relu=relu, algo="sparse_mac", **kw).float()
         assert torch.isfinite(want).any(1)[0]
         assert int((torch.isnan(Y) != torch.isnan(want)).sum()) == 0
