@@ -87,6 +87,10 @@ __device__ __forceinline__ void mfma_acc(f32x4_t& acc, const bf16x8_t a, const b
 }
 __device__ __forceinline__ void mfma_drain() { asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory"); }
 
+// Pin acc's current value in the accumulation registers at this point of the
+// volatile sequence (no code): what comes before mfma_drain() stays before it.
+__device__ __forceinline__ void acc_fence(f32x4_t& acc) { asm volatile("" : "+a"(acc)); }
+
 // XOR of the 16-byte chunk index in staged row r (even: a 32-byte pair stays a pair).
 __device__ __forceinline__ uint32_t swz(uint32_t r) { return 2u * ((r & 3u) | (((r >> 3) & 1u) << 2)); }
 
@@ -227,7 +231,14 @@ void grad_mfma_kernel(GParams p) {
   for (int m = 0; m < T; ++m)
 #pragma unroll
     for (int n = 0; n < 4; ++n) acc[m][n] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-  mfma_drain();
+  const auto fence_all = [&] {
+#pragma unroll
+    for (int m = 0; m < T; ++m)
+#pragma unroll
+      for (int n = 0; n < 4; ++n) acc_fence(acc[m][n]);
+  };
+  fence_all();
+  mfma_drain();  // the zero writes land before the first MFMA reads them
 
   // Step s: the wave waits for its DMAs of the step and meets the others at
   // the barrier (after which nobody reads the previous step's buffer: it is
@@ -263,7 +274,8 @@ void grad_mfma_kernel(GParams p) {
 #pragma unroll
     for (int n = 0; n < 4; ++n) mfma_acc(acc[T - 1][n], a1, b[n]);
   }
-  mfma_drain();
+  mfma_drain();  // the last MFMAs have written acc
+  fence_all();
   lds_barrier();  // every wave is done with the operand buffers
 
   // ---- gather the kept entries ---------------------------------------------------
