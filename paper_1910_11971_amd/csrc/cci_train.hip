@@ -6,14 +6,17 @@
 // by magnitude (larger |w| first, ties to the lower row), marks the n_target
 // lowest as candidates, and drops a candidate when the caller's random word
 // for it is below floor(drop_rate * 2^32).  HBM-bound: reads W and the random
-// words, writes W_eff and the keep mask, all coalesced along c.  Two things
-// kept it from the copy rate: 480 vector instructions a lane for 16 rows
-// ranked against each other, and 128 MB of streamed operands displacing each
-// other in the caches.  The n_target-th smallest magnitude now comes from a
-// sorting network (63 compare-exchanges for 16 rows), and W and the words are
-// read non-temporally: 4096 x 4096, G = 16, 184 MB, 37.6 -> 30.4 us (sort
-// alone 35.1, non-temporal reads alone 33.1; two or four columns a lane 31.5
-// and 37.6).
+// words, writes W_eff and the keep mask, all coalesced along c.  Ranking 16
+// rows against each other took 480 vector instructions a lane; the n_target-th
+// smallest magnitude now comes from a sorting network (63 compare-exchanges for
+// 16 rows).  The streamed operands displace each other in the caches, so rows
+// that start on whole 128-byte lines are read non-temporally (a line shared
+// by two rows would be fetched twice), unless nothing is a candidate: then the
+// random words are not read and W alone stays resident between calls.  us, all
+// pairs compared / sorted / sorted and non-temporal, operands from memory and
+// (in brackets) left in the caches by the call before: 4096 x 4096, G = 16
+// 46.0 / 38.7 / 33.9 (36.8 / 32.2 / 33.0); G = 2 47.7 / 38.9 / 35.5 (33.8 /
+// 31.6 / 33.6); 3072 x 3333, G = 8 33.0 / 29.2 / 27.1 (24.9 / 24.1 / 27.9).
 //
 // cci_grad_packed: gradient of the packed values once the mask is fixed,
 //   dvals[g][k][c] = sum_n dY[n][gG + idx[g][k][c]] * X[n][c].
@@ -62,7 +65,14 @@ __device__ __forceinline__ void sort_keys(uint32_t (&s)[G]) {
           }
 }
 
-template <int G, typename WT>
+template <bool NT, typename T>
+__device__ __forceinline__ T get(const T* p) {
+  return NT ? __builtin_nontemporal_load(p) : *p;
+}
+
+// NT: W and the random words are read non-temporally.  NONE: no candidates,
+// the random words are not read.
+template <int G, bool NT, bool NONE, typename WT>
 __global__ __launch_bounds__(kMaskThreads) void td_mask_fixed(const float* __restrict__ W, const uint32_t* __restrict__ bits,
                                                               int64_t C, int64_t cblocks, int32_t n_target, uint64_t thr,
                                                               WT* __restrict__ We, uint8_t* __restrict__ keep) {
@@ -73,9 +83,18 @@ __global__ __launch_bounds__(kMaskThreads) void td_mask_fixed(const float* __res
   float w[G];
   uint32_t b[G], s[G];
 #pragma unroll
-  for (int r = 0; r < G; ++r) w[r] = __builtin_nontemporal_load(W + (g * G + r) * C + c);
+  for (int r = 0; r < G; ++r) w[r] = get<NT>(W + (g * G + r) * C + c);
+  if constexpr (NONE) {
 #pragma unroll
-  for (int r = 0; r < G; ++r) b[r] = __builtin_nontemporal_load(bits + (g * G + r) * C + c);
+    for (int r = 0; r < G; ++r) {
+      const int64_t o = (g * G + r) * C + c;
+      put<WT>(We, o, w[r]);
+      keep[o] = 1;
+    }
+    return;
+  }
+#pragma unroll
+  for (int r = 0; r < G; ++r) b[r] = get<NT>(bits + (g * G + r) * C + c);
 #pragma unroll
   for (int r = 0; r < G; ++r) s[r] = abs_bits(w[r]);
   sort_keys<G>(s);
@@ -90,7 +109,7 @@ __global__ __launch_bounds__(kMaskThreads) void td_mask_fixed(const float* __res
 #pragma unroll
   for (int r = G - 1; r >= 0; --r) {
     const uint32_t key = abs_bits(w[r]);
-    const bool cand = n_target > 0 && (key < edge || (key == edge && ties > 0));
+    const bool cand = key < edge || (key == edge && ties > 0);
     ties -= key == edge;
     const int64_t o = (g * G + r) * C + c;
     const bool drop = cand && static_cast<uint64_t>(b[r]) < thr;
@@ -130,12 +149,19 @@ hipError_t td_mask_typed(const float* W, int64_t O, int64_t C, int32_t G, int32_
   const int64_t cblocks = (C + kMaskThreads - 1) / kMaskThreads;
   const dim3 grid(static_cast<uint32_t>((O / G) * cblocks));
   const dim3 block(kMaskThreads);
+  const auto launch = [&](auto g) {
+    constexpr int GC = decltype(g)::value;
+    const auto k = n_target == 0 ? td_mask_fixed<GC, false, true, WT>
+                   : C % 32 == 0 ? td_mask_fixed<GC, true, false, WT>
+                                 : td_mask_fixed<GC, false, false, WT>;
+    hipLaunchKernelGGL(k, grid, block, 0, s, W, bits, C, cblocks, n_target, thr, We, keep);
+  };
   switch (G) {
-    case 2: hipLaunchKernelGGL((td_mask_fixed<2, WT>), grid, block, 0, s, W, bits, C, cblocks, n_target, thr, We, keep); break;
-    case 4: hipLaunchKernelGGL((td_mask_fixed<4, WT>), grid, block, 0, s, W, bits, C, cblocks, n_target, thr, We, keep); break;
-    case 8: hipLaunchKernelGGL((td_mask_fixed<8, WT>), grid, block, 0, s, W, bits, C, cblocks, n_target, thr, We, keep); break;
-    case 16: hipLaunchKernelGGL((td_mask_fixed<16, WT>), grid, block, 0, s, W, bits, C, cblocks, n_target, thr, We, keep); break;
-    case 32: hipLaunchKernelGGL((td_mask_fixed<32, WT>), grid, block, 0, s, W, bits, C, cblocks, n_target, thr, We, keep); break;
+    case 2: launch(std::integral_constant<int, 2>{}); break;
+    case 4: launch(std::integral_constant<int, 4>{}); break;
+    case 8: launch(std::integral_constant<int, 8>{}); break;
+    case 16: launch(std::integral_constant<int, 16>{}); break;
+    case 32: launch(std::integral_constant<int, 32>{}); break;
     default:
       hipLaunchKernelGGL((td_mask_generic<WT>), grid, block, 0, s, W, bits, C, cblocks, G, n_target, thr, We, keep);
   }

@@ -146,13 +146,14 @@ def test_training_step_at_the_end_of_the_ramp():
     check_close(to_np_f32(dv), oracle.grad_packed(d, x, ix, G), terms, TOL["bf16"], "dvals")
 
 
+@pytest.mark.parametrize("C", [70, 96])  # rows on whole 128-byte lines are read non-temporally
 @pytest.mark.parametrize("G", [2, 4, 8, 16, 32])
-def test_td_mask_ties_every_candidate_count(G):
+def test_td_mask_ties_every_candidate_count(G, C):
     """Few distinct magnitudes (zeros, signed zeros, infinities among them): the rows equal to the edge are told apart
     by their order, for every number of candidates."""
     need_gpu()
     rng = np.random.default_rng(G)
-    O, C = 2 * G, 70
+    O = 2 * G
     W = rng.choice(np.array([0.0, -0.0, 1.0, -1.0, 2.0, np.inf, -np.inf], np.float32), (O, C))
     for n_t in range(G + 1):
         run_mask(W, G, n_t, rand_bits((O, C), n_t), 0.5, torch.bfloat16)
