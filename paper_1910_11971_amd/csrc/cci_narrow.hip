@@ -369,8 +369,18 @@ __global__ __launch_bounds__(kThreads) void narrow_kernel(NParams p) {
   narrow_body<YT, S, CM, RES>(p, sb);
 }
 
-// Waves of narrow_kernel<YT, S> that fit on the current device at once
-// (queried once per device).
+// Workgroups per CU (waves per SIMD), at most: every wave of the grid expands
+// its slice's weights once, so a third one that fits by a register or two
+// costs more expansions than it hides (fp32 output, 3x3 over 24 channels:
+// 13456 pixels -> 96, K = G = 16, 39 us with two, 51 with three; 72128 -> 32,
+// K = 8 26 / 31).
+template <typename YT, int S, int CM, bool RES>
+constexpr int max_blocks() {
+  return sizeof(YT) == 4 && ((S == 7 && CM == 8) || (S == 4 && CM != 0 && (CM == 8 || RES))) ? 2 : 8;
+}
+
+// Waves of narrow_kernel<YT, S> that fit on the current device at once, at
+// max_blocks per CU (queried once per device).
 template <typename YT, int S, int CM, bool RES>
 int64_t resident_waves() {
   static std::atomic<int64_t> cached[kMaxDevices];
@@ -385,7 +395,7 @@ int64_t resident_waves() {
       hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, reinterpret_cast<const void*>(&narrow_kernel<YT, S, CM, RES>),
                                                    kThreads, 0) == hipSuccess &&
       cus >= 1 && blocks >= 1) {
-    waves = static_cast<int64_t>(cus) * blocks * (kThreads / 64);
+    waves = static_cast<int64_t>(cus) * std::min(blocks, max_blocks<YT, S, CM, RES>()) * (kThreads / 64);
     cached[dev].store(waves, std::memory_order_release);
   }
   return waves;
