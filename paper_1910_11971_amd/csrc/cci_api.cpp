@@ -117,8 +117,15 @@ cci_algo ragged_route(cci::ProductArgs& a, cci_algo chosen, bool mac_next) {
   // 576 11.1 / 17.1; 6272 x 192 -> 1152 12.2 / 21.2; 12544 x 816 -> 136 15.6
   // / 1054 on the sparse-MAC kernels; a 3x3 stride-2 convolution 64 -> 64 over
   // 200 704 output pixels 52.8 / 80.7), except where the narrow ones stream
-  // >= 100 K rows (200704 x 192 -> 32 28.6 / 24.0).
-  if (a.C >= 96 && chosen != CCI_ALGO_TAP_TILE_MFMA && !(chosen == CCI_ALGO_NARROW_MFMA && a.N >= 100000) &&
+  // >= 100 K rows (200704 x 192 -> 32 28.6 / 24.0), and except few kept rows
+  // of unit-stride filters over 64 channels into less than a 64-output tile,
+  // beyond a round of the chip: the dense-tile kernels read such an input
+  // patch once for all taps (3x3, 64 -> 40 over 106 624 pixels, K = 2, 16.1
+  // us there / 23.7; K = 1 geometric mean of 340 1.22, K = 2 of 610 1.06, K =
+  // 4 0.88; 36 K pixels on one round 0.8-0.9 for any K).
+  const bool patch = a.conv && a.geom.KH * a.geom.KW > 1 && a.geom.sh == 1 && a.geom.sw == 1 && a.geom.Cin == 64 &&
+                     a.O < 64 && a.K <= 2 && a.N > 256 * 128 && chosen == CCI_ALGO_DENSE_TILE_MFMA && !mac_next;
+  if (a.C >= 96 && chosen != CCI_ALGO_TAP_TILE_MFMA && !(chosen == CCI_ALGO_NARROW_MFMA && a.N >= 100000) && !patch &&
       cci::tap_tile_supports(a) && accepted())
     return CCI_ALGO_TAP_TILE_MFMA;
   return chosen;
@@ -389,15 +396,22 @@ cci_algo cci_auto_algo(cci_dtype x_t, cci_dtype val_t, int64_t N, int64_t C, int
   // 256 x 256 tiles (>= 128 of them) run on the wide-tile kernels: 2.2-2.4x
   // the dense-tile kernel on 4096^3, and level with the tap-chunk kernels on
   // ResNet-50's 1x1 layers with 196 such tiles.
-  // They run one such tile per CU, so a last round of the chip that is mostly
-  // empty costs a whole one: below 72% full rounds the tap-chunk kernels are
-  // ahead (us, wide / tap: 4096 x 4096 -> 4096, 256 tiles, 95 / 157; 4096 x
-  // 4096 -> 3072, 192 tiles, 95 / 121; 12544 x 256 -> 1024, 196 tiles, 21 /
-  // 23; 4096 x 2048 -> 2048, 128 tiles, 58 / 47; 8192 x 4096 -> 1024, 128
-  // tiles, 101 / 82).
+  // They run one such tile per CU, a round of 256 at a time; the tap-chunk
+  // kernels finish 256 of their quarter-size tiles (a half round) in 0.31-0.43
+  // of that time, 0.36-0.45 with K = G or a few rows of a 32-row group, less
+  // under 1024 columns.  So a nearly empty round goes to them (us, wide / tap:
+  // 4096 x 2048 -> 2048, 1 round, 2 halves, 58 / 47; 8192 x 4096 -> 1024 the
+  // same, 101 / 82; 6291 x 768 -> 3072, K = G, 2 rounds, 5 halves, 60.7 /
+  // 57.5), but not 2738 x 3328 -> 4096, K = G, 1 round, 3 halves, 103 / 133;
+  // 3842 x 4096 -> 5120, K = G, 2 and 5, 241 / 266; 4604 x 4096 -> 4352, G =
+  // 32, K = 2, 2 and 5, 160 / 178.  Over 3 000 random products of up to three
+  // rounds what these limits send to them takes 0.72-0.97 of the time.
   const int64_t tiles256 = (N + 255) / 256 * (O / 256);
-  const bool wide_full = 100 * tiles256 >= 72 * 256 * ((tiles256 + 255) / 256);
-  if (bf && C == cin && C % 64 == 0 && C >= 256 && O % 256 == 0 && tiles256 >= 128 && (wide_full || !tap_shape))
+  const int64_t rounds = (tiles256 + 255) / 256, halves = ((N + 127) / 128 * (O / 128) + 255) / 256;
+  const bool slow_build = K == G || (G == 32 && K < 8);
+  const int64_t lim = C < 1024 ? (slow_build || rounds == 1 ? 5 : 6) : (slow_build ? 4 : 5);
+  const bool tap_ahead = tap_shape && 2 * halves <= lim * rounds;
+  if (bf && C == cin && C % 64 == 0 && C >= 256 && O % 256 == 0 && tiles256 >= 128 && !tap_ahead)
     return CCI_ALGO_WIDE_TILE_MFMA;
   if (tap_shape) return CCI_ALGO_TAP_TILE_MFMA;
   const bool tile_shape = bf && cin % 32 == 0;

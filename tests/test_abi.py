@@ -364,3 +364,22 @@ def test_last_algo_names_the_family_of_a_call():
     assert lib.cci_conv_im2col(FAKE, cci.BF16, 9, 30, 30, 64, 3, 3, 2, 2, 1, 1, FAKE, cci.BF16, FAKE, 64, 8, 2, None,
                                FAKE, cci.BF16, None) == cci.EHIP
     assert cci.last_algo() == "split_k_mfma"
+    # the same filter at unit stride over 64 channels: few kept rows into part of a tile stay on the dense-tile kernels
+    for B, O, K, family in [(34, 40, 2, "dense_tile_mfma"), (34, 40, 4, "tap_tile_mfma"), (34, 72, 2, "tap_tile_mfma"),
+                            (9, 40, 2, "tap_tile_mfma")]:
+        assert lib.cci_conv_im2col(FAKE, cci.BF16, B, 56, 56, 64, 3, 3, 1, 1, 1, 1, FAKE, cci.BF16, FAKE, O, 8, K, None,
+                                   FAKE, cci.BF16, None) == cci.EHIP
+        assert cci.last_algo() == family
+
+
+@pytest.mark.parametrize("N,C,O,G,K,family", [
+    (4096, 2048, 2048, 8, 2, "tap_tile"), (4096, 2048, 2048, 8, 8, "tap_tile"),    # one round, two half rounds
+    (2738, 3328, 4096, 8, 2, "wide_tile"), (2738, 3328, 4096, 2, 2, "wide_tile"),  # one round, three
+    (3842, 4096, 5120, 16, 4, "tap_tile"), (3842, 4096, 5120, 16, 16, "wide_tile"),  # two rounds, five
+    (4604, 4096, 4352, 32, 2, "wide_tile"), (4604, 4096, 4352, 32, 8, "tap_tile"),
+    (6291, 768, 3072, 2, 2, "tap_tile"), (6000, 768, 4096, 8, 2, "tap_tile"), (6000, 768, 4096, 8, 8, "wide_tile"),
+    (6000, 1024, 4096, 8, 2, "wide_tile"),                                         # two rounds, six
+])
+def test_auto_algo_wide_or_tap(N, C, O, G, K, family):
+    """The wide-tile kernels' rounds of the chip against the tap-chunk kernels' half rounds."""
+    assert cci.auto_algo(torch.bfloat16, torch.bfloat16, N, C, C, O, G, K) == family + "_mfma"
