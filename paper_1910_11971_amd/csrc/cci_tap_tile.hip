@@ -255,7 +255,10 @@ __device__ __forceinline__ void tap_tile_body(const TParams& p, uint8_t* const l
   int cur_kh = static_cast<int>(static_cast<uint32_t>(cur_t) * p.kw_mul >> 16), cur_kw = cur_t - cur_kh * p.KW;
   uint32_t xv[KEEP ? 4 : 1];
   const auto tap_off = [&](int i) {
-    return static_cast<uint32_t>(xbase[i] + (cur_kh * p.W + cur_kw) * p.Cin * 2) | (((xinv[i] >> cur_t) & 1u) << 31);
+    // (after the last of 32 taps cur_t is 32: only a dead chunk, every bit of
+    // its xinv set, still loads)
+    return static_cast<uint32_t>(xbase[i] + (cur_kh * p.W + cur_kw) * p.Cin * 2) |
+           (((xinv[i] >> (cur_t & 31)) & 1u) << 31);
   };
   auto set_tap = [&] {
     if constexpr (KEEP) {

@@ -189,6 +189,8 @@ TAP_CASES = [  # B, H, W, Cin, O, KH, KW, stride, pad, G, K
     (4, 9, 9, 64, 256, 3, 3, 2, 1, 2, 1),      # G = 2: 16 packed rows per wave
     (2, 11, 13, 192, 128, 3, 3, 1, 1, 8, 3),   # 12 packed rows per wave; 3 channel blocks per tap
     (1, 20, 20, 64, 128, 7, 4, 1, 3, 16, 1),   # 28 taps, padding 3
+    (1, 20, 20, 64, 128, 8, 4, 1, 3, 16, 1),   # 32 taps
+    (2, 3, 40, 64, 128, 1, 32, 1, 0, 8, 2),    # 32 taps in a row
     (6, 16, 16, 64, 128, 1, 1, 1, 0, 4, 2),    # 1x1 through the conv call; 16 packed rows per wave
     (3, 4, 4, 64, 128, 3, 3, 1, 1, 1, 1),      # G = 1
     (1, 1, 1, 64, 128, 3, 3, 1, 1, 8, 2),      # one pixel: every tap but the centre in the padding
