@@ -322,17 +322,17 @@ cci_algo cci_auto_algo(cci_dtype x_t, cci_dtype val_t, int64_t N, int64_t C, int
   // packed bytes set the time, and the few-row kernel (one expanded 16 x 32
   // tile per k-step and wave, read once) takes 7-24 us on a 4096 x 4096
   // layer where the tile kernels need 55-70 us.
-  // (A ragged last tile, O % 16 != 0, stays on the tile kernels: ResNet-50's
-  // 64 x 2048 -> 1000 classifier inside the forward, its 6 MB of weights
-  // cold, takes 35.5 us here against 27.1 us on the dense-tile kernel; 18.9
-  // us here with the weights warm in cache.)
+  // (A ragged last tile, O % 16 != 0, is left to the rules below and to
+  // ragged_route: ResNet-50's dense 64 x 2048 -> 1000 classifier inside the
+  // forward, its 6 MB of weights cold, takes 35.5 us here against 27.1 us on
+  // the dense-tile kernel; 18.9 us here with the weights warm in cache.)
   if (x_t == CCI_BF16 && val_t == CCI_BF16 && C == cin && N <= 64 && C % 32 == 0 && O % 16 == 0)
     return CCI_ALGO_FEW_ROWS_MFMA;
   // 3x3 convolutions over 32 or 64 channels into 32 or 64 outputs: their
   // whole expanded tile fits in registers, so it is expanded once per
   // workgroup and only activations stream (measured 2-3x the dense-tile
   // kernel on a 32 x 56 x 56 x 64 -> 64 layer).  Only unit stride is taken:
-  // other strides run on the dense-tile kernels.
+  // other strides go on as dense-tile products (run_product, ragged_route).
   if (x_t == CCI_BF16 && val_t == CCI_BF16 && (cin == 32 || cin == 64) && C == 9 * cin && (O == 32 || O == 64) &&
       O % G == 0)
     return CCI_ALGO_RESIDENT_MFMA;
@@ -381,13 +381,14 @@ cci_algo cci_auto_algo(cci_dtype x_t, cci_dtype val_t, int64_t N, int64_t C, int
   // 160: 10.8 vs 19.5 us; 512 x 512 -> 320: 4.9 vs 7.9 us; 256 x 1024 ->
   // 160: 6.1 vs 12.0 us); else, with O % 64 == 0, the tap-chunk kernels'
   // 64-output tiles (960 -> 320: 13.6 us vs 15.4 split, 20.8 dense-tile).
-  // From 12 544 rows on the dense-tile kernels stay ahead (576 -> 96: 14.6
-  // vs 20.2 us; 384 -> 64: 8.7 vs 9.1 tap, 9.5 split).  O % 128 == 0 keeps
-  // the routes below (tap-chunk or wide-tile), measured on ResNet-50.
+  // From 12 544 rows on they are dense-tile products by shape, which
+  // ragged_route gives to the tap-chunk kernels (576 -> 96: 9.2 us, dense-tile
+  // 14.1, split 17.7).  O % 128 == 0 keeps the routes below (tap-chunk or
+  // wide-tile), measured on ResNet-50.
   if (x_t == CCI_BF16 && val_t == CCI_BF16 && C == cin && C >= 512 && C <= 1024 && C % 32 == 0 && O % 16 == 0 &&
       O % 128 != 0) {
-    // (at C = 512 two k-steps per wave: half a round at most; 4096 x 512 ->
-    // 96 is 9.0 us split, 8.3 us dense-tile)
+    // (half a round at C = 512 here; ragged_route takes the whole one with K
+    // <= 4: 4096 x 512 -> 96 7.2 us split, 8.1 us dense-tile)
     const int64_t t64x32 = (N + 63) / 64 * ((O + 31) / 32);
     if (t64x32 <= (C >= 576 ? 256 : 128) && K <= 4) return CCI_ALGO_SPLIT_K_MFMA;
     if (O % 64 == 0 && G <= 16 && 16 % G == 0 && (2 * K <= G || K == G)) return CCI_ALGO_TAP_TILE_MFMA;

@@ -28,7 +28,7 @@
 // bf16 inputs widen exactly; products and sums are fp32.
 // Bound by the LDS (96 KiB of transposing reads a step at ~320 B/ns per CU,
 // 0.3 of the 0.85 us) and the matrix cores (0.5 us).  us, with the reads
-// through the compiler's builtin / now: 4096 x 4096 x 4096 177 / 113, 2048 x
+// through the compiler's builtin / now: 4096 x 4096 x 4096 177 / 114, 2048 x
 // 2048 x 2048 89 / 27, 4096 samples of 1024 x 1024 173 / 49.
 #include "cci_device.hpp"
 #include "cci_launch.hpp"
