@@ -48,7 +48,9 @@ int main() {
   const int before = g_launches;
   // valid calls reach exactly one launcher each
   EXPECT(cci_pack((const float*)A, 64, 32, 8, 2, B, CCI_BF16, (uint8_t*)C, nullptr) == CCI_OK);
+  EXPECT(cci_last_algo() == CCI_ALGO_AUTO);
   EXPECT(cci_spmm(A, CCI_BF16, 16, 64, B, CCI_BF16, (const uint8_t*)C, 64, 8, 2, nullptr, D, CCI_BF16, nullptr) == CCI_OK);
+  EXPECT(cci_last_algo() == CCI_ALGO_FEW_ROWS_MFMA);
   EXPECT(cci_spmm_algo(A, CCI_F32, 16, 64, B, CCI_F32, (const uint8_t*)C, 64, 8, 2, nullptr, D, CCI_F32,
                        CCI_ALGO_SPARSE_MAC, nullptr) == CCI_OK);
   EXPECT(cci_conv_im2col(A, CCI_BF16, 1, 8, 8, 32, 3, 3, 1, 1, 1, 1, B, CCI_BF16, (const uint8_t*)C, 64, 8, 2,
