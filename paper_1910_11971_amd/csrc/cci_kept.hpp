@@ -28,20 +28,26 @@ __device__ __forceinline__ float kept_sum(const P& p, int32_t K, int32_t n, int3
   }
   float s = 0.0f;
 #pragma unroll 1
-  for (int32_t c = lane; c < p.C; c += 64) {
-    int64_t at = static_cast<int64_t>(n) * p.C + c;
-    bool in = true;
-    if constexpr (CONV) {
-      const int32_t t = c / p.Cin, kh = t / p.KW, ih = ih0 + kh, iw = iw0 + t - kh * p.KW;
-      in = ih >= 0 && ih < p.H && iw >= 0 && iw < p.W;
-      at = ((static_cast<int64_t>(img) * p.H + ih) * p.W + iw) * p.Cin + (c - t * p.Cin);
-    }
-    const float x = in ? bf16_to_f32(p.X[at]) : 0.0f;
+  for (int32_t c0 = 0; c0 < p.C; c0 += 64) {  // (the same trips for every lane)
+    const int32_t c = c0 + lane;
+    if (c < p.C) {
+      int64_t at = static_cast<int64_t>(n) * p.C + c;
+      bool in = true;
+      if constexpr (CONV) {
+        const int32_t t = c / p.Cin, kh = t / p.KW, ih = ih0 + kh, iw = iw0 + t - kh * p.KW;
+        in = ih >= 0 && ih < p.H && iw >= 0 && iw < p.W;
+        at = ((static_cast<int64_t>(img) * p.H + ih) * p.W + iw) * p.Cin + (c - t * p.Cin);
+      }
+      const float x = in ? bf16_to_f32(p.X[at]) : 0.0f;
 #pragma unroll 1
-    for (int32_t k = 0; k < K; ++k) {
-      const int64_t q = (static_cast<int64_t>(g) * K + k) * p.C + c;
-      if ((K == p.G ? k : static_cast<int32_t>(p.idx[q])) == slot) s = __builtin_fmaf(bf16_to_f32(p.vals[q]), x, s);
+      for (int32_t k = 0; k < K; ++k) {
+        const int64_t q = (static_cast<int64_t>(g) * K + k) * p.C + c;
+        if ((K == p.G ? k : static_cast<int32_t>(p.idx[q])) == slot) s = __builtin_fmaf(bf16_to_f32(p.vals[q]), x, s);
+      }
     }
+    // a NaN, or infinities of both signs, settle the sum: inputs full of them
+    // end after a trip or two
+    if (__any(s != s) || (__any(s == __builtin_inff()) && __any(s == -__builtin_inff()))) return __builtin_nanf("");
   }
 #pragma unroll
   for (int off = 32; off >= 1; off /= 2) s += __shfl_xor(s, off, 64);

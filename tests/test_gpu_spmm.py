@@ -420,6 +420,7 @@ def test_spmm_auto_nonfinite_reaches_kept_columns_only(family, case, y_dtype):
     bad = torch.tensor([float("inf"), float("-inf"), float("nan")], device=DEV).bfloat16()
     X[rows, cols] = bad[torch.arange(len(rows), device=DEV) % 3]
     X[1] = float("nan")  # a whole row
+    X[3, ::2], X[3, 1::2] = float("inf"), float("-inf")
     X[N - 1, C - 1] = float("inf")
     X[N - 1, 0] = float("-inf")
     s, b, r, r_t, _ = rand_epilogue(O, N, y_dtype, N + O, residual=True)
